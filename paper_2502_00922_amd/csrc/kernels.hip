@@ -801,6 +801,46 @@ struct GemvArgs {
   uint32_t B;         // batch rows
 };
 
+// ---- products split over blocks: partial sums through the workspace
+// Partial sums are stored and loaded as relaxed agent-scope atomics, which
+// are performed at the memory all XCDs share, past the per-XCD caches. A
+// store has been performed once vmcnt no longer counts it, so the wave waits
+// for its stores before it counts itself in; nothing else passes between the
+// blocks. (A release fence at agent scope also writes the whole L2 back: a
+// 1000x4096 product over 4 k-parts took 16.5 us with it, 12.4 us without.)
+__device__ inline void part_store(float* p, float v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Counts the wave's block in (its partial sums, stored by this wave, first);
+// true for the last of the KS blocks, whose later loads see every part. The
+// counter is back at zero then.
+__device__ inline bool last_to_arrive(uint32_t* counter, uint32_t KS, uint32_t lane) {
+  wait_vm0();
+  uint32_t old = 0;
+  if (lane == 0) old = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  old = (uint32_t)__builtin_amdgcn_readfirstlane((int)old);
+  asm volatile("" ::: "memory");  // the parts are loaded after the count is known
+  if (old != KS - 1) return false;
+  if (lane == 0) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return true;
+}
+
+// Sum of the KS parts at p, p + stride, ... in order; eight loads in flight
+// (one at a time, each part costs a round trip to memory).
+__device__ inline float part_sum(const float* p, uint64_t stride, uint32_t KS) {
+  float t = 0.f;
+  for (uint32_t k0 = 0; k0 < KS; k0 += 8) {
+    float v[8];
+#pragma unroll
+    for (uint32_t j = 0; j < 8; ++j)
+      v[j] = __hip_atomic_load(p + min(k0 + j, KS - 1) * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (uint32_t j = 0; j < 8; ++j) t = k0 + j < KS ? t + v[j] : t;
+  }
+  return t;
+}
+
 // Copies x[b][c0*S .. (c0+GC)*S) for every batch row into xs ([batch][GC*S]).
 template <int B, bool XBF16>
 __device__ inline void issue_x(const GemvArgs& p, uint32_t* xs, uint32_t c0, uint32_t lane) {
@@ -950,34 +990,17 @@ __global__ void __launch_bounds__(1024) gemv_kernel(GemvArgs p) {
     return;
   }
   // Several blocks share this row block: publish the partial sums, and the
-  // last block to arrive adds them in k-part order and resets the counter.
-  // Partials are written and read with agent-scope atomics; the counter
-  // increment is an agent-scope acquire-release, so the parts stored before
-  // it (release) are visible to the block that sees the last count
-  // (acquire, then a fence for the lanes that did not take part in it).
+  // last block to arrive adds them in k-part order.
   const uint32_t ldp = a.RB * a.GR;
   if (lane < G)
 #pragma unroll
-    for (int b = 0; b < B; ++b)
-      __hip_atomic_store(p.partial + ((uint64_t)kp * B + b) * ldp + r0 + lane, s[b], __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // every lane's parts, before the count
-  uint32_t old = 0;
-  if (lane == 0) old = __hip_atomic_fetch_add(p.counter + rb, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-  old = __shfl(old, 0, 64);
-  if (old != p.KS - 1) return;
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // every lane reads the parts published before the count
+    for (int b = 0; b < B; ++b) part_store(p.partial + ((uint64_t)kp * B + b) * ldp + r0 + lane, s[b]);
+  if (!last_to_arrive(p.counter + rb, p.KS, lane)) return;
   if (lane < G) {
 #pragma unroll
-    for (int b = 0; b < B; ++b) {
-      float t = 0.f;
-      for (uint32_t k = 0; k < p.KS; ++k)
-        t += __hip_atomic_load(p.partial + ((uint64_t)k * B + b) * ldp + r0 + lane, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-      p.y[(uint64_t)b * ldy + r0 + lane] = t;
-    }
+    for (int b = 0; b < B; ++b)
+      p.y[(uint64_t)b * ldy + r0 + lane] = part_sum(p.partial + (uint64_t)b * ldp + r0 + lane, (uint64_t)B * ldp, p.KS);
   }
-  if (lane == 0) __hip_atomic_store(p.counter + rb, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ------------------------------------------------------------------ fused GEMV on matrix cores
@@ -1021,27 +1044,15 @@ __device__ inline void mfma_finish(const GemvArgs& p, const f32x4_t& acc, float*
   if (nb_ok)
 #pragma unroll
     for (int v = 0; v < 4; ++v)
-      if (4 * q + v < G)
-        __hip_atomic_store(p.partial + ((uint64_t)kp * p.B + n) * ldp + r0 + 4 * q + v, s[v], __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // every lane's parts, before the count
-  uint32_t old = 0;
-  if (lane == 0) old = __hip_atomic_fetch_add(p.counter + rb, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-  old = __shfl(old, 0, 64);
-  if (old != p.KS - 1) return;
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // every lane reads the parts published before the count
+      if (4 * q + v < G) part_store(p.partial + ((uint64_t)kp * p.B + n) * ldp + r0 + 4 * q + v, s[v]);
+  if (!last_to_arrive(p.counter + rb, p.KS, lane)) return;
   if (nb_ok) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      if (4 * q + v >= G) continue;
-      float t = 0.f;
-      for (uint32_t k = 0; k < p.KS; ++k)
-        t += __hip_atomic_load(p.partial + ((uint64_t)k * p.B + n) * ldp + r0 + 4 * q + v, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-      p.y[(uint64_t)n * ldy + r0 + 4 * q + v] = t;
-    }
+    for (int v = 0; v < 4; ++v)
+      if (4 * q + v < G)
+        p.y[(uint64_t)n * ldy + r0 + 4 * q + v] =
+            part_sum(p.partial + (uint64_t)n * ldp + r0 + 4 * q + v, (uint64_t)p.B * ldp, p.KS);
   }
-  if (lane == 0) __hip_atomic_store(p.counter + rb, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Fused decode-GEMV for 16-row groups (GR = 16, GC = 4) and bf16 x, on the
@@ -2567,29 +2578,23 @@ static uint64_t xtile_region(const hl_tensor* t, uint32_t batch) {
 static uint64_t counter_bytes(uint32_t RB) { return ((uint64_t)RB * 4 + 255) & ~255ull; }
 
 // Column blocks per block (*C) and blocks per row block (*KS) of the
-// non-persistent kernels: enough blocks to fill the device, each wave
-// decoding at least one group.
+// non-persistent kernels. A block of up to 8 waves decodes a group each in
+// little more than the time of one, and meeting the other parts through
+// memory costs 2.5 to 3 us: a row block of at most 8 column blocks is one
+// block (1024x1024, 4 column blocks: 7.8 us as one block, 16.7 us in four
+// parts at the time, 10.0 in two). Longer ones are split into parts of 4 or
+// more, as many as keep every part on a CU of its own (1000x4096: 11.3 us in
+// 4 parts, 12.3 whole; 256x8192: 11.5 in 8, 18.9 whole; more parts than CUs
+// lose: 3500x4096 12.8 us whole, 16.0 in two).
+constexpr uint32_t kWholeColumnBlocks = 8, kPartColumnBlocks = 4;
 static void split_shape(const Plan& pl, uint32_t* C_out, uint32_t* KS_out) {
   const uint32_t CB = pl.ga.CB, RB = pl.ga.RB;
   const uint32_t cus = (uint32_t)device_cus();
-  const uint64_t target_waves = (uint64_t)cus * 16;
-  const uint32_t gpw = (uint32_t)std::max<uint64_t>(1, ((uint64_t)RB * CB + target_waves - 1) / target_waves);
-  uint32_t C = std::min<uint32_t>(CB, pl.waves * gpw);
-  uint32_t KS = (CB + C - 1) / C;
-  // a matrix with fewer row blocks than CUs: split its columns further, so
-  // that every CU gets a block (narrower blocks, one group per wave)
-  if ((uint64_t)RB * KS < cus) {
-    KS = std::min<uint32_t>(CB, (cus + RB - 1) / RB);
-    C = (CB + KS - 1) / KS;
-    KS = (CB + C - 1) / C;
-  }
-  if (KS > ks_cap(CB)) {
-    KS = ks_cap(CB);
-    C = (CB + KS - 1) / KS;
-    KS = (CB + C - 1) / C;
-  }
-  *C_out = C;
-  *KS_out = KS;
+  uint32_t KS = 1;
+  if (CB > kWholeColumnBlocks)
+    KS = std::max<uint32_t>(1, std::min({cus / RB, (CB + kPartColumnBlocks - 1) / kPartColumnBlocks, ks_cap(CB)}));
+  *C_out = (CB + KS - 1) / KS;
+  *KS_out = (CB + *C_out - 1) / *C_out;
 }
 
 // Workspace bytes of a split over KS k-parts (counters and partial sums).
