@@ -1366,7 +1366,33 @@ static_assert(HL_LUT_BYTES == kTab16MaxWords * 4, "the table buffer holds the la
 // which builds them, and in the kernels, which read them).
 struct Tab16 {
   uint32_t bits[3], base[3], aux, words;  // per field (ml, e, mh): window bits, word offset
+  bool flat;  // the joint layout of flat mh codes: tables 0 = (ml, e) and 1 = e, no table 2
 };
+
+// Float16 weights whose mh codes all have 5 bits (flat; the mantissa bits of
+// a trained matrix are near uniform, so Huffman coding leaves them so): the
+// canonical code of mh is mh itself, read from the window by a bit reversal,
+// its place known from the lengths of the other two. One table then decodes
+// (ml, e) together from a window of kJoint16Bits bits (or the longest ml code,
+// if longer; fewer if the two codes never need them):
+//   the code bits of the weight (ml, e and the 5 of mh) in bits 0..4, ml in
+//   bits 16..20, e in bits 26..30;
+// where the two codes are longer than the window (one weight in 300 of such
+// matrices), ml's code bits and ml, and bit 31; table 1, in 16-bit entries,
+// then has the code bits of e and mh in bits 0..4 and e in bits 10..14. A
+// chain of one LDS round trip per weight instead of three: 14336x4096 54.7 us
+// against 80.6 us. A 12- or 13-bit window saves 1 to 2% of large products,
+// but two blocks of 8 waves no longer fit a CU (5000x2048 26.0 us).
+constexpr uint32_t kJoint16Bits = 11;
+constexpr uint32_t kFlatBits = 5;
+constexpr uint32_t kMiss16 = 1u << 31;
+
+static bool flat_mh(const hl_codebook16& cb) {
+  if (cb.mh.nsym != 32) return false;
+  for (int s = 0; s < 32; ++s)
+    if (cb.mh.len[s] != kFlatBits) return false;
+  return true;
+}
 
 static Tab16 tab16_layout(const hl_codebook16& cb) {
   Tab16 t;
@@ -1377,8 +1403,12 @@ static Tab16 tab16_layout(const hl_codebook16& cb) {
     if (f[k]->nsym > 1)
       for (int s = 0; s < 32; ++s) L = std::max<uint32_t>(L, f[k]->len[s]);
     t.bits[k] = L;
+  }
+  t.flat = flat_mh(cb);
+  if (t.flat) t.bits[0] = std::min(std::max(kJoint16Bits, t.bits[0]), t.bits[0] + t.bits[1]);
+  for (int k = 0; k < (t.flat ? 2 : 3); ++k) {
     t.base[k] = off;
-    off += 1u << L;
+    off += t.flat && k == 1 ? ((1u << t.bits[k]) + 1) / 2 : 1u << t.bits[k];
   }
   t.aux = off;
   t.words = (off + kAux16Words + 3) & ~3u;
@@ -1400,15 +1430,27 @@ static Aux16 make_aux16(const hl_codebook16& cb) {
 
 __global__ void __launch_bounds__(256) lut16_kernel(uint32_t* lut, Aux16 aux, Tab16 lay) {
   const uint32_t auxoff[3] = {kAuxMl, kAuxE, kAuxMh}, shift[3] = {16, 26, 21};
-  for (int f = 0; f < 3; ++f) {
+  const uint32_t t0 = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
+  for (uint32_t v = t0; lay.flat && v < 1u << lay.bits[0]; v += nt) {
+    uint32_t ub = 0, ue = 0;
+    const int ml = max(field_from_bits(aux.w + kAuxMl, v, lay.bits[0], &ub), 0);
+    const int e = field_from_bits(aux.w + kAuxE, v >> ub, lay.bits[0] - ub, &ue);
+    lut[lay.base[0] + v] = ((uint32_t)ml << 16) | (e < 0 ? kMiss16 | ub : ((uint32_t)e << 26) | (ub + ue + kFlatBits));
+  }
+  for (uint32_t v = t0; lay.flat && v < 1u << lay.bits[1]; v += nt) {
+    uint32_t ue = 0;
+    const int e = max(field_from_bits(aux.w + kAuxE, v, lay.bits[1], &ue), 0);
+    reinterpret_cast<uint16_t*>(lut + lay.base[1])[v] = (uint16_t)(((uint32_t)e << 10) | (ue + kFlatBits));
+  }
+  for (int f = lay.flat ? 3 : 0; f < 3; ++f) {
     const uint32_t n = 1u << lay.bits[f];
-    for (uint32_t v = threadIdx.x; v < n; v += blockDim.x) {
+    for (uint32_t v = t0; v < n; v += nt) {
       uint32_t u = 0;
       const int sym = field_from_bits(aux.w + auxoff[f], v, lay.bits[f], &u);
       lut[lay.base[f] + v] = sym < 0 ? kEsc16 : (u | ((uint32_t)sym << shift[f]));
     }
   }
-  for (uint32_t i = lay.aux + threadIdx.x; i < lay.words; i += blockDim.x)
+  for (uint32_t i = lay.aux + t0; i < lay.words; i += nt)
     lut[i] = i - lay.aux < (uint32_t)kAux16Words ? aux.w[i - lay.aux] : 0u;
 }
 
@@ -1517,20 +1559,93 @@ __device__ inline void decode8_f16(const GroupArgs& a, const uint32_t* sc, uint3
   pos2 = p;
 }
 
+// Positions with flat mh codes are column bit positions minus 11: a window's
+// low 11 bits are old ones, of which the last five (bits 6..10) are the mh of
+// the weight before, and reversing the low word puts that mh at bits 21..25,
+// its place in a decoded weight.
+constexpr uint32_t kFlatOld = 11;
+
+// Entry of the flat layout's e table for the window w (its index at bits 1.. of w).
+__device__ inline uint32_t flat_e(const GroupArgs& a, uint32_t w) {
+  return *reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(s_dyn) + a.t16_base[1] +
+                                            (w & a.t16_mask[1]));
+}
+
+// Four weights with flat mh codes from four column words: h[0..3] as in
+// decode2_f16; p advanced by the four whole entries; bit 7 of flag set when
+// they have more than the 85 code bits that the words are sure to hold, or
+// the last two more than the 53 new bits of a 64-bit window. The first two
+// take at most 58 bits, and their table windows lie within those 53; the rest
+// of the window is then followed by the next 32 bits. A code cut off at the
+// end of the window reads zero bits there and decodes as one that reaches
+// past the end too, so the counts show it.
+__device__ inline void decode4_flat(const GroupArgs& a, const uint32_t* sc, uint32_t jmax, uint32_t& p,
+                                    uint32_t& flag, uint32_t* h) {
+  const uint32_t j = min((p & kPosMask16) >> 5, jmax - 1);
+  const uint32_t w0 = col_word(sc, j), w1 = col_word(sc, j + 1), w2 = col_word(sc, j + 2), w3 = col_word(sc, j + 3);
+  uint64_t W = funnel64(w2, w1, w0, p);
+  const uint32_t t = __builtin_amdgcn_alignbit(w3, w2, p);
+  uint32_t used = 0, two = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    uint32_t ent = tab16<0>(a, (uint32_t)W >> (kFlatOld - 2));
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64((int)ent < 0) != 0, 0)) {
+      const uint32_t e = flat_e(a, (uint32_t)(shift_window(W, ent) >> (kFlatOld - 1)));
+      ent = (int)ent < 0 ? (ent ^ kMiss16) + (e & 31u) + ((e & 0x7C00u) << 16) : ent;
+    }
+    W = shift_window(W, ent);
+    used += ent;
+    if (k == 1) {
+      two = used;
+      W |= (uint64_t)t << ((0u - two) & 63u);  // 64 - (bits of the two weights, 10 to 58)
+    }
+    h[k] = (ent & 0x7C1F0000u) | (__builtin_bitreverse32((uint32_t)W) & 0x03E00000u);
+  }
+  flag |= ((used & 0xFFu) + (127 - (96 - kFlatOld))) | (((used - two) & 0xFFu) + (127 - (64 - kFlatOld)));
+  p += used;
+}
+
+// decode8_f16 with flat mh codes (positions minus 11).
+__device__ inline void decode8_flat(const GroupArgs& a, const uint32_t* sc, uint32_t sc_off, uint32_t jmax,
+                                    uint32_t& pos, uint32_t* h) {
+  const uint32_t p0 = pos;
+  uint32_t p = p0, flag = 0;
+  decode4_flat(a, sc, jmax, p, flag, h);
+  decode4_flat(a, sc, jmax, p, flag, h + 4);
+  if (__builtin_expect((flag & 0x80u) != 0, 0)) {
+    const Dec8 d = decode8_f16_careful(sc_off, jmax, (p0 & kPosMask16) + kFlatOld - 2, a.t16_aux);
+    p = d.pos2 - (kFlatOld - 2);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) h[k] = d.h[k];
+  }
+  pos = p;
+}
+
+template <bool FLAT>
+__device__ inline void decode8_half(const GroupArgs& a, const uint32_t* sc, uint32_t sc_off, uint32_t jmax,
+                                    uint32_t& pos, uint32_t* h) {
+  if constexpr (FLAT) decode8_flat(a, sc, sc_off, jmax, pos, h); else decode8_f16(a, sc, sc_off, jmax, pos, h);
+}
+// What a lane's position (column bit position minus 2) loses in each form.
+template <bool FLAT>
+constexpr uint32_t kHalfOld = FLAT ? kFlatOld - 2 : 0;
+
 // Eight float16 weights packed in pairs (weight 2m in the low half of dword
-// m) from their decoded bits and the step's sign byte (bit k: weight k).
+// m) from their decoded bits and the step's sign byte (bit k: weight k; the
+// byte twice, 15 bits apart, has the signs of each pair 16 bits apart).
 __device__ inline uint4 pack8_f16(const uint32_t* h, uint32_t sb) {
+  const uint32_t s2 = sb | (sb << 15);
   uint32_t d[4];
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    const uint32_t v = __builtin_amdgcn_perm(h[2 * m + 1], h[2 * m], 0x07060302u) & 0x7FFF7FFFu;
-    d[m] = v | (((sb >> (2 * m)) & 1u) << 15) | (((sb >> (2 * m + 1)) & 1u) << 31);
-  }
+  for (int m = 0; m < 4; ++m)
+    d[m] = (__builtin_amdgcn_perm(h[2 * m + 1], h[2 * m], 0x07060302u) & 0x7FFF7FFFu) |
+           ((s2 << (15 - 2 * m)) & 0x80008000u);
   return uint4{d[0], d[1], d[2], d[3]};
 }
 
 // Decode to float16 bits; waves take groups in turn; region per wave: the
 // stream columns. Signs are read straight from the sign plane.
+template <bool FLAT>
 __global__ void __launch_bounds__(1024) decode16_kernel(GroupArgs a, uint16_t* out) {
   const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t waves = blockDim.x >> 6;
@@ -1548,7 +1663,7 @@ __global__ void __launch_bounds__(1024) decode16_kernel(GroupArgs a, uint16_t* o
   load_tables16(a);
   __syncthreads();
   for (; g < n_grp; g += stride) {
-    uint32_t pos2 = issue_stream(a, cols, m, lane);
+    uint32_t pos2 = issue_stream(a, cols, m, lane) - kHalfOld<FLAT>;
     const Meta cur = m;
     if (g + stride < n_grp) m = load_meta(a, g + stride, lane);
     wait_vm0();
@@ -1559,7 +1674,7 @@ __global__ void __launch_bounds__(1024) decode16_kernel(GroupArgs a, uint16_t* o
       const uint8_t* sg = a.raw + (cur.first + lane) * sb_per_seg;
       for (uint32_t t = 0; t < a.S; t += 8) {
         uint32_t h[8];
-        decode8_f16(a, sc, sc_off, jmax, pos2, h);
+        decode8_half<FLAT>(a, sc, sc_off, jmax, pos2, h);
         *reinterpret_cast<uint4*>(o + t) = pack8_f16(h, sg[t >> 3]);
       }
     }
@@ -1599,7 +1714,7 @@ struct Signs {
 // structure (lane 16q + i decodes row i of segment q; the A operand is its 8
 // weights, the B operand x[n = i][8 activations]), with the float16 decode
 // (two table reads per weight) and one sign load per lane and group.
-template <int SP, bool XT>
+template <int SP, bool XT, bool FLAT>
 __global__ void __launch_bounds__(1024) gemv16_mfma_kernel(GemvArgs p) {
   constexpr int KP = SP < 8 ? SP : SP == 8 ? 8 : 4;
   const GroupArgs& a = p.g;
@@ -1637,7 +1752,7 @@ __global__ void __launch_bounds__(1024) gemv16_mfma_kernel(GemvArgs p) {
   }
   asm volatile("" : "+v"(m.nbw), "+v"(m.u0)::"memory");
   table16_dma(a);
-  uint32_t pos2 = issue_stream(a, cols, m, lane);
+  uint32_t pos2 = issue_stream(a, cols, m, lane) - kHalfOld<FLAT>;
   wait_vm0();
   __syncthreads();
 
@@ -1661,7 +1776,7 @@ __global__ void __launch_bounds__(1024) gemv16_mfma_kernel(GemvArgs p) {
 #pragma unroll
       for (int k = 0; k < KP; ++k) {
         uint32_t h[8];
-        decode8_f16(a, sc, sc_off, jmax, pd, h);
+        decode8_half<FLAT>(a, sc, sc_off, jmax, pd, h);
         const uint4 wv = pack8_f16(h, sgc.byte(t0 + k));
         acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, wv),
                                                      __builtin_bit_cast(f16x8_t, xv[k]), acc, 0, 0, 0);
@@ -1674,7 +1789,7 @@ __global__ void __launch_bounds__(1024) gemv16_mfma_kernel(GemvArgs p) {
     if (more) {
       m = mn;
       mn = load_meta(a, rb * a.CB + (cb + 2 * waves < cb_end ? cb + 2 * waves : cb + waves), lane);
-      pos2 = issue_stream(a, cols, m, lane);
+      pos2 = issue_stream(a, cols, m, lane) - kHalfOld<FLAT>;
       sg.load(a.raw + (m.first + mu) * SP);
     }
   }
@@ -1724,7 +1839,8 @@ __device__ inline const GemvArgs& gemv_args(const Args& x) {
 // TB selects the decode table: 0 the joint table (bf16 formats), 1 the
 // bounded-pair table (split format, pairs of at most kBpBits bits), 2 the
 // float16 format's three field tables (at the start of the dynamic LDS, its
-// sign plane instead of raw bytes, the float16 matrix instruction).
+// sign plane instead of raw bytes, the float16 matrix instruction), 3 the
+// same with flat mh codes.
 // NT = 16-token tiles of activations per matrix instruction step: 1 (up to 16
 // activation rows), or 2 or 4 for prefill products of 17 to 32 or 33 to 64
 // tokens (one bf16 matrix, activations from their tiled copy).
@@ -1737,7 +1853,8 @@ constexpr uint32_t stream_threads(bool dec, int tb, int nt = 1) {
 
 template <int SP, int JT, bool XT, class Args, bool DEC, int TB, int NT = 1>
 __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kernel(Args sa) {
-  constexpr bool BP = TB == 1, F16 = TB == 2;
+  constexpr bool BP = TB == 1, F16 = TB >= 2, FLAT = TB == 3;
+  constexpr uint32_t kOld = BP ? kBpShift - 2 : kHalfOld<FLAT>;  // positions: column bit positions minus 2 + kOld
   constexpr uint32_t S = SP * 8;
   constexpr uint32_t kRows = JT + 1, kBuf = kRows * kCol;
   static_assert(JT % 4 == 0 && kBuf >= 256, "layout");
@@ -1817,7 +1934,7 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
   Meta m1 = load_meta(a, g1, lane);
   if constexpr (BP) bp_table_store(te);
   u32x4_a4 sw[JT / 4];
-  uint32_t pos2 = stream_load<JT>(a, m0, lane, sw) - (BP ? kBpShift - 2 : 0u);
+  uint32_t pos2 = stream_load<JT>(a, m0, lane, sw) - kOld;
   uint2 rw[F16 ? 1 : SP];  // raw bytes of the next group's steps (bf16 formats)
   Signs<SP> sg, sgn;       // float16: the lane's sign bytes of this and the next group
   uint4 xv[SP];
@@ -1888,7 +2005,7 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
       const uint32_t n_c0 = m1.c0;
       // the next group's stream words (this group's again after the last),
       // then the metadata of the group after it
-      uint32_t pos2n = stream_load<JT>(a, m1, lane, sw) - (BP ? kBpShift - 2 : 0u);
+      uint32_t pos2n = stream_load<JT>(a, m1, lane, sw) - kOld;
       m1 = load_meta(a, g2, lane);
       // prefetch source: the next group, else the lane's cached activations
       // (decoding: the current group's raw bytes)
@@ -1909,7 +2026,7 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
         uint4 wv;
         if constexpr (F16) {
           uint32_t h[8];
-          decode8_f16(a, sc, sc_off, jmax, pd, h);
+          decode8_half<FLAT>(a, sc, sc_off, jmax, pd, h);
           wv = pack8_f16(h, sg.byte(k));
         } else {
           uint32_t e[8];
@@ -1965,7 +2082,7 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
         }
       }
       if constexpr (F16) sg = sgn;
-      if constexpr (DEC && F16) {
+      if constexpr (DEC && F16 && !FLAT) {
         // float16 (its decode already LDS-bound: the transposition below cost
         // 5% there): row r0 + i, columns (c0 + q)*S .. + S back to back
         if (i < G) {
@@ -2173,7 +2290,7 @@ static hl_status make_plan(const hl_tensor* t, uint32_t extra_words_per_wave, bo
   if (is_fp16(t)) {
     const Tab16 lay = tab16_layout(t->cb16);
     for (int k = 0; k < 3; ++k) {
-      a.t16_mask[k] = ((1u << lay.bits[k]) - 1) << 2;
+      a.t16_mask[k] = ((1u << lay.bits[k]) - 1) << (lay.flat && k == 1 ? 1 : 2);
       a.t16_base[k] = lay.base[k] * 4;
     }
     a.t16_aux = lay.aux;
@@ -2311,29 +2428,36 @@ static hl_status launch_stream(bool xt, bool bp, uint32_t seg_len, int jt, bool 
 
 // The float16 format on the persistent kernel (one matrix, float16 x; with
 // DEC its decode to float16).
-template <bool XT, bool DEC>
+template <bool XT, bool DEC, int TB>
 static hl_status launch_stream16_x(uint32_t seg_len, int jt, dim3 grid, dim3 block, size_t lds, hipStream_t s,
                                    const GemvArgs& g) {
   if (seg_len == 64) {
     switch (jt) {
-      case 24: return launch(gemv_stream_kernel<8, 24, XT, GemvArgs, DEC, 2>, grid, block, lds, s, g);
-      case 28: return launch(gemv_stream_kernel<8, 28, XT, GemvArgs, DEC, 2>, grid, block, lds, s, g);
-      case 32: return launch(gemv_stream_kernel<8, 32, XT, GemvArgs, DEC, 2>, grid, block, lds, s, g);
+      case 24: return launch(gemv_stream_kernel<8, 24, XT, GemvArgs, DEC, TB>, grid, block, lds, s, g);
+      case 28: return launch(gemv_stream_kernel<8, 28, XT, GemvArgs, DEC, TB>, grid, block, lds, s, g);
+      case 32: return launch(gemv_stream_kernel<8, 32, XT, GemvArgs, DEC, TB>, grid, block, lds, s, g);
       default: return HL_EUNSUPPORTED;
     }
   }
   switch (jt) {
-    case 12: return launch(gemv_stream_kernel<4, 12, XT, GemvArgs, DEC, 2>, grid, block, lds, s, g);
-    case 16: return launch(gemv_stream_kernel<4, 16, XT, GemvArgs, DEC, 2>, grid, block, lds, s, g);
+    case 12: return launch(gemv_stream_kernel<4, 12, XT, GemvArgs, DEC, TB>, grid, block, lds, s, g);
+    case 16: return launch(gemv_stream_kernel<4, 16, XT, GemvArgs, DEC, TB>, grid, block, lds, s, g);
     default: return HL_EUNSUPPORTED;
   }
 }
 
-static hl_status launch_stream16(bool xt, bool dec, uint32_t seg_len, int jt, dim3 grid, dim3 block, size_t lds,
-                                 hipStream_t s, const GemvArgs& g) {
-  if (dec) return launch_stream16_x<false, true>(seg_len, jt, grid, block, lds, s, g);
-  return xt ? launch_stream16_x<true, false>(seg_len, jt, grid, block, lds, s, g)
-            : launch_stream16_x<false, false>(seg_len, jt, grid, block, lds, s, g);
+template <int TB>
+static hl_status launch_stream16_tb(bool xt, bool dec, uint32_t seg_len, int jt, dim3 grid, dim3 block, size_t lds,
+                                    hipStream_t s, const GemvArgs& g) {
+  if (dec) return launch_stream16_x<false, true, TB>(seg_len, jt, grid, block, lds, s, g);
+  return xt ? launch_stream16_x<true, false, TB>(seg_len, jt, grid, block, lds, s, g)
+            : launch_stream16_x<false, false, TB>(seg_len, jt, grid, block, lds, s, g);
+}
+
+static hl_status launch_stream16(bool xt, bool dec, bool flat, uint32_t seg_len, int jt, dim3 grid, dim3 block,
+                                 size_t lds, hipStream_t s, const GemvArgs& g) {
+  return flat ? launch_stream16_tb<3>(xt, dec, seg_len, jt, grid, block, lds, s, g)
+              : launch_stream16_tb<2>(xt, dec, seg_len, jt, grid, block, lds, s, g);
 }
 
 // Decoding to bf16 with the persistent kernel (p.y = the output).
@@ -2462,7 +2586,7 @@ extern "C" hl_status hl_tensor_prepare(const hl_tensor* t, void* stream) {
   if (!t || !t->lut_dev) return HL_EINVAL;
   if (t->format == HL_FORMAT_FP16) {
     if (!code16_valid(t->cb16)) return HL_ECORRUPT;
-    return launch(lut16_kernel, dim3(1), dim3(256), 0, (hipStream_t)stream, t->lut_dev, make_aux16(t->cb16),
+    return launch(lut16_kernel, dim3(16), dim3(256), 0, (hipStream_t)stream, t->lut_dev, make_aux16(t->cb16),
                   tab16_layout(t->cb16));
   }
   if (t->format == HL_FORMAT_WHOLE_EXPONENT) {
@@ -2501,6 +2625,11 @@ static bool bounded_pairs(const hl_tensor* t) {
   return t->seg_len == 64 && longest_exponent_code(t) <= (uint32_t)kBpBits;
 }
 
+// The persistent kernel's decode table for a matrix (its TB).
+static int stream_table(const hl_tensor* t) {
+  return is_fp16(t) ? (flat_mh(t->cb16) ? 3 : 2) : bounded_pairs(t) ? 1 : 0;
+}
+
 static bool stream_shape(const hl_tensor* t, const GroupArgs& ga, int* jt, uint32_t* waves, size_t* per_wave) {
   if (t->grp_rows != 16 || (t->seg_len != 64 && t->seg_len != 32)) return false;
   const uint32_t CB = ga.CB, RB = ga.RB, cus = (uint32_t)device_cus();
@@ -2509,16 +2638,17 @@ static bool stream_shape(const hl_tensor* t, const GroupArgs& ga, int* jt, uint3
                      : bounded_pairs(t) ? (size_t)kBpWords * 4
                                         : (size_t)(kLutN + kAuxWords) * 4;
   *per_wave = (size_t)(*jt + 1) * kCol * 4;
-  uint32_t w = std::min<uint32_t>(kMaxWaves, stream_threads(false, is_fp16(t) ? 2 : 0) / 64);
+  uint32_t w = std::min<uint32_t>(kMaxWaves, stream_threads(false, stream_table(t)) / 64);
   while (w > 1 && tab + w * *per_wave > kMaxLds) --w;
   // fewer waves per block when that gives every wave two groups: the
   // second group's loads then overlap the first one's decode
   while (w > 8 && (uint64_t)RB * CB < 2ull * cus * w) --w;
   *waves = w;
-  // float16: two row blocks per CU at least (4096x4096, one per CU: 25.9 us
-  // against 24.3 us on the non-persistent kernel; 14336x4096 65.8 against
-  // 86.2 us)
-  const uint32_t min_rb = is_fp16(t) ? 2 * cus : cus;
+  // float16 without flat mh codes: two row blocks per CU at least (4096x4096,
+  // one per CU: 25.9 us against 24.3 us on the non-persistent kernel;
+  // 14336x4096 65.8 against 86.2 us). With them one is enough (4096x4096 20.2
+  // against 20.3 us; decoding 4096x11008 55.8 against 98.8 us).
+  const uint32_t min_rb = stream_table(t) == 2 ? 2 * cus : cus;
   return *jt && w >= 8 && CB >= w && RB >= min_rb && (uint64_t)RB * CB >= 2ull * cus * w;
 }
 
@@ -2541,11 +2671,11 @@ extern "C" hl_status hl_decode(const hl_tensor* t, uint16_t* out_dev, void* stre
     p.C = pl.ga.CB;
     p.KS = 1;
     // the kernel's bound when decoding (registers for a group's weights)
-    w = stream_threads(true, is_fp16(t) ? 2 : 0) / 64;
+    w = stream_threads(true, stream_table(t)) / 64;
     const dim3 grid(std::min<uint32_t>(pl.ga.RB, (uint32_t)device_cus()));
     // float16: its tables lead the dynamic LDS
     if (is_fp16(t))
-      return launch_stream16(false, true, t->seg_len, jt, grid, dim3(w * 64),
+      return launch_stream16(false, true, flat_mh(t->cb16), t->seg_len, jt, grid, dim3(w * 64),
                              (size_t)pl.ga.t16_words * 4 + w * per_wave, (hipStream_t)stream, p);
     // the bounded-pair table where the encoder's joint limit holds (with the
     // whole-row stores it decodes 28672x8192 in 175.9 us against 187.7 us
@@ -2557,8 +2687,10 @@ extern "C" hl_status hl_decode(const hl_tensor* t, uint16_t* out_dev, void* stre
   if (is_fp16(t)) {
     const uint32_t per_cu = std::max<uint32_t>(1, std::min<uint32_t>(8, kMaxLds / (uint32_t)pl.lds));
     const uint32_t blocks = std::min<uint32_t>((n_grp + pl.waves - 1) / pl.waves, device_cus() * per_cu);
-    return launch(decode16_kernel, dim3(blocks), dim3(pl.waves * 64), pl.lds, (hipStream_t)stream, pl.ga,
-                  out_dev);
+    return flat_mh(t->cb16) ? launch(decode16_kernel<true>, dim3(blocks), dim3(pl.waves * 64), pl.lds,
+                                     (hipStream_t)stream, pl.ga, out_dev)
+                            : launch(decode16_kernel<false>, dim3(blocks), dim3(pl.waves * 64), pl.lds,
+                                     (hipStream_t)stream, pl.ga, out_dev);
   }
   const uint32_t per_cu =
       std::max<uint32_t>(1, std::min<uint32_t>(8, kMaxLds / (uint32_t)(pl.lds + (kLutN + kAuxWords) * 4)));
@@ -2634,23 +2766,26 @@ static hl_status choose_split(const hl_tensor* t, const Plan& pl, uint32_t batch
   return HL_OK;
 }
 
-template <bool XT>
+template <bool XT, bool FLAT>
 static hl_status launch_mfma16_x(uint32_t steps, dim3 grid, dim3 block, size_t lds, hipStream_t s,
                                  const GemvArgs& p) {
   switch (steps) {
-    case 1: return launch(gemv16_mfma_kernel<1, XT>, grid, block, lds, s, p);
-    case 2: return launch(gemv16_mfma_kernel<2, XT>, grid, block, lds, s, p);
-    case 4: return launch(gemv16_mfma_kernel<4, XT>, grid, block, lds, s, p);
-    case 8: return launch(gemv16_mfma_kernel<8, XT>, grid, block, lds, s, p);
-    case 16: return launch(gemv16_mfma_kernel<16, XT>, grid, block, lds, s, p);
+    case 1: return launch(gemv16_mfma_kernel<1, XT, FLAT>, grid, block, lds, s, p);
+    case 2: return launch(gemv16_mfma_kernel<2, XT, FLAT>, grid, block, lds, s, p);
+    case 4: return launch(gemv16_mfma_kernel<4, XT, FLAT>, grid, block, lds, s, p);
+    case 8: return launch(gemv16_mfma_kernel<8, XT, FLAT>, grid, block, lds, s, p);
+    case 16: return launch(gemv16_mfma_kernel<16, XT, FLAT>, grid, block, lds, s, p);
     default: return HL_EUNSUPPORTED;
   }
 }
 
-static hl_status launch_mfma16(bool xt, uint32_t steps, dim3 grid, dim3 block, size_t lds, hipStream_t s,
+static hl_status launch_mfma16(bool xt, bool flat, uint32_t steps, dim3 grid, dim3 block, size_t lds, hipStream_t s,
                                const GemvArgs& p) {
-  return xt ? launch_mfma16_x<true>(steps, grid, block, lds, s, p)
-            : launch_mfma16_x<false>(steps, grid, block, lds, s, p);
+  if (flat)
+    return xt ? launch_mfma16_x<true, true>(steps, grid, block, lds, s, p)
+              : launch_mfma16_x<false, true>(steps, grid, block, lds, s, p);
+  return xt ? launch_mfma16_x<true, false>(steps, grid, block, lds, s, p)
+            : launch_mfma16_x<false, false>(steps, grid, block, lds, s, p);
 }
 
 // Larger batches on the matrix cores read the activations from a tiled copy
@@ -2701,7 +2836,7 @@ static hl_status gemv16(const hl_tensor* t, const void* x_dev, uint32_t batch, f
     if (st != HL_OK) return st;
     p.C = pl.ga.CB;
     p.KS = 1;
-    return launch_stream16(xt, false, t->seg_len, jt, dim3(std::min<uint32_t>(pl.ga.RB, (uint32_t)device_cus())),
+    return launch_stream16(xt, false, flat_mh(t->cb16), t->seg_len, jt, dim3(std::min<uint32_t>(pl.ga.RB, (uint32_t)device_cus())),
                            dim3(w * 64), (size_t)pl.ga.t16_words * 4 + w * per_wave, stream, p);
   }
   st = choose_split(t, pl, batch, workspace_dev, workspace_bytes, clear, stream, &p, &w);
@@ -2711,7 +2846,7 @@ static hl_status gemv16(const hl_tensor* t, const void* x_dev, uint32_t batch, f
   const dim3 grid(pl.ga.RB * p.KS), block(w * 64);
   // the reduction reuses the wave regions: 4 floats per lane per wave
   const size_t lds = std::max<size_t>(pl.lds_for(w), (size_t)pl.ga.t16_words * 4 + (size_t)w * 4 * 64 * 4);
-  return launch_mfma16(xt, t->seg_len / 8, grid, block, lds, stream, p);
+  return launch_mfma16(xt, flat_mh(t->cb16), t->seg_len / 8, grid, block, lds, stream, p);
 }
 
 // Which kernel family a product runs on and its plan: 16-row groups with
