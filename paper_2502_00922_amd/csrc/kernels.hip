@@ -26,9 +26,11 @@
 #include <hipblaslt/hipblaslt.h>
 
 #include <algorithm>
-#include <type_traits>
+#include <atomic>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
+#include <unordered_map>
 
 #include "hl_internal.h"
 #include "hufflm.h"
@@ -2233,15 +2235,47 @@ __global__ void __launch_bounds__(1024) gemv_bf16_kernel(const uint16_t* w, cons
 
 // ------------------------------------------------------------------ launch helpers
 
+constexpr int kMaxDevices = 64;
+
+// The current GPU's compute units; asked of the runtime once per GPU (a
+// launch's plan needs them several times).
 static int device_cus() {
+  static std::atomic<int> known[kMaxDevices];
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 256;
+  const bool keep = dev >= 0 && dev < kMaxDevices;
+  if (keep && (cus = known[dev].load(std::memory_order_relaxed)) > 0) return cus;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     return 256;
+  if (keep) known[dev].store(cus, std::memory_order_relaxed);
   return cus;
 }
 
 constexpr uint32_t kMaxLds = 160 * 1024;
+
+// Raises a kernel's dynamic LDS limit on the current GPU to at least `lds`
+// bytes; the limit it was last raised to is kept per GPU and kernel, since
+// raising it costs more than the rest of a launch's host work.
+static bool allow_lds(const void* kernel, size_t lds) {
+  static std::mutex mu;
+  static std::unordered_map<const void*, size_t> limit[kMaxDevices];
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  auto raise = [&] {
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
+  };
+  if (dev < 0 || dev >= kMaxDevices) return raise();
+  try {
+    std::lock_guard<std::mutex> lock(mu);
+    size_t& have = limit[dev][kernel];
+    if (have >= lds) return true;
+    if (!raise()) return false;
+    have = lds;
+    return true;
+  } catch (...) {  // no memory for the entry
+    return raise();
+  }
+}
 
 struct Plan {
   GroupArgs ga;
@@ -2312,9 +2346,7 @@ static hl_status make_plan(const hl_tensor* t, uint32_t extra_words_per_wave, bo
 template <class K, class... A>
 static hl_status launch(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s, A... args) {
   if (lds + (kLutN + kAuxWords) * 4 > 64 * 1024) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-      return HL_EHIP;
+    if (!allow_lds(reinterpret_cast<const void*>(kernel), lds)) return HL_EHIP;
   }
   hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
   return hipGetLastError() == hipSuccess ? HL_OK : HL_EHIP;
@@ -2983,7 +3015,6 @@ extern "C" hl_status hl_decode_gemv(const hl_tensor* t, const void* x_dev, hl_dt
 // hipGetSymbolAddress (with that GPU current) and is what the kernels get.
 static __device__ __align__(256) uint8_t scratch[HL_NOALLOC_SCRATCH_BYTES];
 
-constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mu;
 static void* g_scratch[kMaxDevices];
 

@@ -229,9 +229,12 @@ def validate(blob) -> int:
 
 
 def _stream_ptr(stream=None):
+    """hipStream_t of `stream`, or of the current device's current stream (its
+    raw handle: building torch's stream object for it takes 3 us a call)."""
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dev_arg(t, name: str, dtypes=None, shape=None, numel: int = 0):
@@ -297,8 +300,8 @@ class DeviceTensor:
         self.blob = torch.from_numpy(blob).to(device)
         self.lut = torch.empty(LUT_BYTES // 4, dtype=torch.int32, device=device)
         self.view = TensorView()
-        _check(lib().hl_tensor_view(ctypes.c_void_p(self.blob.data_ptr()), blob.ctypes.data, blob.size,
-                                    ctypes.c_void_p(self.lut.data_ptr()), ctypes.byref(self.view)),
+        _check(lib().hl_tensor_view(self.blob.data_ptr(), blob.ctypes.data, blob.size,
+                                    self.lut.data_ptr(), ctypes.byref(self.view)),
                "hl_tensor_view")
         _check(lib().hl_tensor_prepare(ctypes.byref(self.view), _stream_ptr(stream)), "hl_tensor_prepare")
 
@@ -329,18 +332,21 @@ class DeviceTensor:
             out = torch.empty((R, K), dtype=torch.int16, device=self.blob.device)
         _dev_arg(out, "out", (torch.int16, torch.bfloat16, torch.float16), numel=R * K)
         _on_device(self.blob.device, out=out)
-        _check(lib().hl_decode(ctypes.byref(self.view), ctypes.c_void_p(out.data_ptr()), _stream_ptr(stream)),
+        _check(lib().hl_decode(ctypes.byref(self.view), out.data_ptr(), _stream_ptr(stream)),
                "hl_decode")
         return out
 
     def workspace(self, batch: int = MAX_BATCH):
         """Zeroed device workspace for gemv at up to ``batch`` rows (cached)."""
         import torch
-        need = int(lib().hl_gemv_workspace_bytes(ctypes.byref(self.view), batch))
         ws = getattr(self, "_ws", None)
+        if ws is not None and batch <= getattr(self, "_ws_batch", 0):
+            return ws
+        need = int(lib().hl_gemv_workspace_bytes(ctypes.byref(self.view), batch))
         if ws is None or ws.numel() < need:
             ws = torch.zeros(max(need, 4), dtype=torch.uint8, device=self.blob.device)
             self._ws = ws
+        self._ws_batch = batch  # need grows with the batch
         return ws
 
     def gemv(self, x, y=None, stream=None, workspace=None):
@@ -360,10 +366,10 @@ class DeviceTensor:
         _on_device(dev, x=x, y=y, workspace=workspace)
         if workspace is None:
             workspace = self.workspace()
-        ws_ptr, ws_n = (None, 0) if workspace is False else (ctypes.c_void_p(workspace.data_ptr()),
-                                                              workspace.numel() * workspace.element_size())
-        _check(lib().hl_decode_gemv(ctypes.byref(self.view), ctypes.c_void_p(x.data_ptr()), dt, x.shape[0],
-                                    ctypes.c_void_p(y.data_ptr()), ws_ptr, ws_n, _stream_ptr(stream)),
+        ws_ptr, ws_n = ((None, 0) if workspace is False
+                        else (workspace.data_ptr(), workspace.numel() * workspace.element_size()))
+        _check(lib().hl_decode_gemv(ctypes.byref(self.view), x.data_ptr(), dt, x.shape[0],
+                                    y.data_ptr(), ws_ptr, ws_n, _stream_ptr(stream)),
                "hl_decode_gemv")
         return y
 
@@ -375,8 +381,8 @@ class DeviceTensor:
         x = _check_x(x, K)
         _dev_arg(y, "y", (torch.float32,), numel=x.shape[0] * R)
         _on_device(self.blob.device, x=x, y=y)
-        _check(lib().hl_decode_gemv_noalloc(ctypes.byref(self.view), ctypes.c_void_p(x.data_ptr()), _x_dtype(x),
-                                            x.shape[0], ctypes.c_void_p(y.data_ptr()), _stream_ptr(stream)),
+        _check(lib().hl_decode_gemv_noalloc(ctypes.byref(self.view), x.data_ptr(), _x_dtype(x),
+                                            x.shape[0], y.data_ptr(), _stream_ptr(stream)),
                "hl_decode_gemv_noalloc")
         return y
 
@@ -399,8 +405,8 @@ class DeviceTensor:
         if ws is None or ws.numel() < need:
             ws = torch.zeros(max(need, 4), dtype=torch.uint8, device=self.blob.device)
             self._gemm_ws = ws
-        _check(lib().hl_decode_gemm(ctypes.byref(self.view), ctypes.c_void_p(x.data_ptr()), HL_BF16, T,
-                                    ctypes.c_void_p(y.data_ptr()), ctypes.c_void_p(ws.data_ptr()), ws.numel(),
+        _check(lib().hl_decode_gemm(ctypes.byref(self.view), x.data_ptr(), HL_BF16, T,
+                                    y.data_ptr(), ws.data_ptr(), ws.numel(),
                                     _stream_ptr(stream)), "hl_decode_gemm")
         return y
 
@@ -430,14 +436,12 @@ def gemv_multi(tensors, x, ys=None, stream=None, workspace=None):
     _on_device(dev, x=x, workspace=workspace, **{f"ys[{m}]": y for m, y in enumerate(ys)})
     if workspace is None:
         workspace = max((t.workspace() for t in tensors), key=lambda w: w.numel())
-    ws_ptr, ws_n = (None, 0) if workspace is False else (ctypes.c_void_p(workspace.data_ptr()),
-                                                          workspace.numel() * workspace.element_size())
-    views = (ctypes.POINTER(TensorView) * len(tensors))(*[ctypes.pointer(t.view) for t in tensors])
+    ws_ptr, ws_n = ((None, 0) if workspace is False
+                    else (workspace.data_ptr(), workspace.numel() * workspace.element_size()))
+    views = (ctypes.c_void_p * len(tensors))(*[ctypes.addressof(t.view) for t in tensors])
     outs = (ctypes.c_void_p * len(tensors))(*[y.data_ptr() for y in ys])
-    _check(lib().hl_decode_gemv_multi(ctypes.cast(views, ctypes.c_void_p), len(tensors),
-                                      ctypes.c_void_p(x.data_ptr()), dt, x.shape[0],
-                                      ctypes.cast(outs, ctypes.c_void_p), ws_ptr, ws_n, _stream_ptr(stream)),
-           "hl_decode_gemv_multi")
+    _check(lib().hl_decode_gemv_multi(views, len(tensors), x.data_ptr(), dt, x.shape[0], outs, ws_ptr, ws_n,
+                                      _stream_ptr(stream)), "hl_decode_gemv_multi")
     return ys
 
 
@@ -456,6 +460,6 @@ def gemv_bf16(w, x, y=None, stream=None):
         y = torch.empty((x.shape[0], R), dtype=torch.float32, device=x.device)
     _dev_arg(y, "y", (torch.float32,), numel=x.shape[0] * R)
     _on_device(w.device if w.is_cuda else None, w=w, x=x, y=y)
-    _check(lib().hl_gemv_bf16(ctypes.c_void_p(w.data_ptr()), R, K, ctypes.c_void_p(x.data_ptr()), dt,
-                              x.shape[0], ctypes.c_void_p(y.data_ptr()), _stream_ptr(stream)), "hl_gemv_bf16")
+    _check(lib().hl_gemv_bf16(w.data_ptr(), R, K, x.data_ptr(), dt,
+                              x.shape[0], y.data_ptr(), _stream_ptr(stream)), "hl_gemv_bf16")
     return y
