@@ -3194,45 +3194,66 @@ static hl_status lt_handle(hipblasLtHandle_t* out) {
 // Y[n][r] = sum_k W[r][k] X[n][k] from bf16 W [rows][cols] and X [tokens][cols]
 // into float32 Y [tokens][rows]: in column-major terms D (rows x tokens, ld
 // rows) = A^T B with A = W as a cols x rows matrix and B = X as cols x tokens.
-// No GEMM workspace (an algorithm that needs none), so nothing is cleared on
-// the stream.
-static hl_status gemm_bf16_lt(const uint16_t* w, const uint16_t* x, float* y, uint64_t rows, uint64_t cols,
-                              uint32_t tokens, hipStream_t stream) {
+// No GEMM workspace, so nothing is cleared on the stream.
+struct LtGemm {
   hipblasLtHandle_t h = nullptr;
-  hl_status st = lt_handle(&h);
-  if (st != HL_OK) return st;
   hipblasLtMatmulDesc_t op = nullptr;
   hipblasLtMatrixLayout_t la = nullptr, lb = nullptr, ld = nullptr;
-  hipblasLtMatmulPreference_t pref = nullptr;
-  st = HL_EHIP;
-  const hipblasOperation_t ta = HIPBLAS_OP_T, tb = HIPBLAS_OP_N;
-  const uint64_t no_ws = 0;
-  hipblasLtMatmulHeuristicResult_t heur[1];
-  int found = 0;
-  const float alpha = 1.f, beta = 0.f;
-  if (hipblasLtMatmulDescCreate(&op, HIPBLAS_COMPUTE_32F, HIP_R_32F) == HIPBLAS_STATUS_SUCCESS &&
-      hipblasLtMatmulDescSetAttribute(op, HIPBLASLT_MATMUL_DESC_TRANSA, &ta, sizeof(ta)) == HIPBLAS_STATUS_SUCCESS &&
-      hipblasLtMatmulDescSetAttribute(op, HIPBLASLT_MATMUL_DESC_TRANSB, &tb, sizeof(tb)) == HIPBLAS_STATUS_SUCCESS &&
-      hipblasLtMatrixLayoutCreate(&la, HIP_R_16BF, cols, rows, (int64_t)cols) == HIPBLAS_STATUS_SUCCESS &&
-      hipblasLtMatrixLayoutCreate(&lb, HIP_R_16BF, cols, tokens, (int64_t)cols) == HIPBLAS_STATUS_SUCCESS &&
-      hipblasLtMatrixLayoutCreate(&ld, HIP_R_32F, rows, tokens, (int64_t)rows) == HIPBLAS_STATUS_SUCCESS &&
-      hipblasLtMatmulPreferenceCreate(&pref) == HIPBLAS_STATUS_SUCCESS &&
-      hipblasLtMatmulPreferenceSetAttribute(pref, HIPBLASLT_MATMUL_PREF_MAX_WORKSPACE_BYTES, &no_ws,
-                                            sizeof(no_ws)) == HIPBLAS_STATUS_SUCCESS) {
-    if (hipblasLtMatmulAlgoGetHeuristic(h, op, la, lb, ld, ld, pref, 1, heur, &found) != HIPBLAS_STATUS_SUCCESS ||
-        found < 1)
-      st = HL_EUNSUPPORTED;
-    else if (hipblasLtMatmul(h, op, &alpha, w, la, x, lb, &beta, y, ld, y, ld, &heur[0].algo, nullptr, 0,
-                             stream) == HIPBLAS_STATUS_SUCCESS)
-      st = HL_OK;
+  hipblasLtMatmulAlgo_t algo;
+
+  ~LtGemm() {
+    if (ld) hipblasLtMatrixLayoutDestroy(ld);
+    if (lb) hipblasLtMatrixLayoutDestroy(lb);
+    if (la) hipblasLtMatrixLayoutDestroy(la);
+    if (op) hipblasLtMatmulDescDestroy(op);
   }
-  if (pref) hipblasLtMatmulPreferenceDestroy(pref);
-  if (ld) hipblasLtMatrixLayoutDestroy(ld);
-  if (lb) hipblasLtMatrixLayoutDestroy(lb);
-  if (la) hipblasLtMatrixLayoutDestroy(la);
-  if (op) hipblasLtMatmulDescDestroy(op);
-  return st;
-}
+
+  // Finds an algorithm that needs no workspace; HL_EUNSUPPORTED if the
+  // library offers none. The library is asked with room for any workspace: an
+  // algorithm that divides the sums over blocks then says how much its
+  // partial tiles take, while asked with no room it answers with the same
+  // algorithm and a need of zero, and stores them past a null pointer
+  // (2605x22784 at 200 tokens: 28.9 MB). `deep`: look beyond the first answer
+  // (60 us of host time, against 2).
+  hl_status find(uint64_t rows, uint64_t cols, uint32_t tokens, bool deep) {
+    hl_status st = lt_handle(&h);
+    if (st != HL_OK) return st;
+    const hipblasOperation_t ta = HIPBLAS_OP_T, tb = HIPBLAS_OP_N;
+    const uint64_t room = 1ull << 40;
+    constexpr int kDeep = 16;
+    hipblasLtMatmulHeuristicResult_t heur[kDeep];
+    hipblasLtMatmulPreference_t pref = nullptr;
+    st = HL_EHIP;
+    if (hipblasLtMatmulDescCreate(&op, HIPBLAS_COMPUTE_32F, HIP_R_32F) == HIPBLAS_STATUS_SUCCESS &&
+        hipblasLtMatmulDescSetAttribute(op, HIPBLASLT_MATMUL_DESC_TRANSA, &ta, sizeof(ta)) == HIPBLAS_STATUS_SUCCESS &&
+        hipblasLtMatmulDescSetAttribute(op, HIPBLASLT_MATMUL_DESC_TRANSB, &tb, sizeof(tb)) == HIPBLAS_STATUS_SUCCESS &&
+        hipblasLtMatrixLayoutCreate(&la, HIP_R_16BF, cols, rows, (int64_t)cols) == HIPBLAS_STATUS_SUCCESS &&
+        hipblasLtMatrixLayoutCreate(&lb, HIP_R_16BF, cols, tokens, (int64_t)cols) == HIPBLAS_STATUS_SUCCESS &&
+        hipblasLtMatrixLayoutCreate(&ld, HIP_R_32F, rows, tokens, (int64_t)rows) == HIPBLAS_STATUS_SUCCESS &&
+        hipblasLtMatmulPreferenceCreate(&pref) == HIPBLAS_STATUS_SUCCESS &&
+        hipblasLtMatmulPreferenceSetAttribute(pref, HIPBLASLT_MATMUL_PREF_MAX_WORKSPACE_BYTES, &room,
+                                              sizeof(room)) == HIPBLAS_STATUS_SUCCESS) {
+      st = HL_EUNSUPPORTED;
+      for (int ask = 1; st != HL_OK && ask <= (deep ? kDeep : 1); ask += kDeep - 1) {
+        int found = 0;
+        if (hipblasLtMatmulAlgoGetHeuristic(h, op, la, lb, ld, ld, pref, ask, heur, &found) != HIPBLAS_STATUS_SUCCESS)
+          break;
+        for (int k = 0; k < std::min(found, ask) && st != HL_OK; ++k)
+          if (heur[k].workspaceSize == 0) algo = heur[k].algo, st = HL_OK;
+      }
+    }
+    if (pref) hipblasLtMatmulPreferenceDestroy(pref);
+    return st;
+  }
+
+  hl_status run(const uint16_t* w, const uint16_t* x, float* y, hipStream_t stream) {
+    const float alpha = 1.f, beta = 0.f;
+    return hipblasLtMatmul(h, op, &alpha, w, la, x, lb, &beta, y, ld, y, ld, &algo, nullptr, 0, stream) ==
+                   HIPBLAS_STATUS_SUCCESS
+               ? HL_OK
+               : HL_EHIP;
+  }
+};
 
 template <int SP>
 static hl_status launch_gemm_sp(uint32_t nt, dim3 grid, size_t lds, hipStream_t s, const GemmArgs& p) {
@@ -3302,12 +3323,19 @@ extern "C" hl_status hl_decode_gemm(const hl_tensor* t, const void* x_dev, hl_dt
     }
   }
   if (tokens > kGemmFusedMaxTokens) {
-    // many tokens: decode once (bit-exact bf16 in the workspace), then the GEMM
-    uint16_t* w = reinterpret_cast<uint16_t*>(workspace_dev);
-    const hl_status st = hl_decode(t, w, stream);
-    if (st != HL_OK) return st;
-    return gemm_bf16_lt(w, reinterpret_cast<const uint16_t*>(x_dev), y_dev, t->rows, t->cols, tokens,
-                        (hipStream_t)stream);
+    // many tokens: decode once (bit-exact bf16 in the workspace), then the
+    // GEMM; the fused kernel where the library has none without a workspace
+    // (few output tiles and long sums). One chunk of tokens decodes the
+    // matrix once there as well, so only more than that is worth a deep look.
+    LtGemm lt;
+    hl_status st = lt.find(t->rows, t->cols, tokens, tokens > kGemmMaxTiles * kTile);
+    if (st == HL_OK) {
+      uint16_t* w = reinterpret_cast<uint16_t*>(workspace_dev);
+      st = hl_decode(t, w, stream);
+      if (st != HL_OK) return st;
+      return lt.run(w, reinterpret_cast<const uint16_t*>(x_dev), y_dev, (hipStream_t)stream);
+    }
+    if (st != HL_EUNSUPPORTED) return st;
   }
   Plan pl;
   hl_status st = make_plan(t, 0, false, &pl);
@@ -3336,6 +3364,10 @@ extern "C" hl_status hl_decode_gemm(const hl_tensor* t, const void* x_dev, hl_dt
   // give two blocks per CU; else split so that they do (one block fits a CU).
   const uint64_t base = (uint64_t)p.RS * chunks, target = 2ull * device_cus();
   p.cpb = base >= target ? CB : std::max<uint32_t>(1, (uint32_t)(CB * base / target));
+  // as many ranges as the workspace holds partial sums of (up to 64 tokens it
+  // holds all; beyond, it has the size of the decoded weights)
+  const uint64_t room = std::max<uint64_t>(1, workspace_bytes / ((uint64_t)tokens * t->rows * 4));
+  p.cpb = std::max<uint32_t>(p.cpb, (uint32_t)((CB + room - 1) / room));
   p.KS = (CB + p.cpb - 1) / p.cpb;
   p.partial = reinterpret_cast<float*>(workspace_dev);
   const uint64_t blocks = (uint64_t)p.KS * base;
