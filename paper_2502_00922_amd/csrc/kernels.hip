@@ -3174,11 +3174,21 @@ extern "C" size_t hl_gemm_workspace_bytes(const hl_tensor* t, uint32_t tokens) {
   return (size_t)(CB * tokens * t->rows * 4);
 }
 
-// One hipBLASLt handle per GPU, created on first use with that GPU current.
+// One hipBLASLt handle per GPU, created on first use with that GPU current,
+// and the algorithms last chosen there (see LtGemm::find), by size.
+struct LtChoice {
+  uint64_t rows, cols;
+  uint32_t tokens;  // 0: no entry
+  bool found;
+  hipblasLtMatmulAlgo_t algo;
+};
+constexpr int kLtChoices = 64;
 static std::mutex g_lt_mu;
 static hipblasLtHandle_t g_lt[kMaxDevices];
+static LtChoice g_lt_choice[kMaxDevices][kLtChoices];
+static uint32_t g_lt_next[kMaxDevices];  // the entry that the next choice takes
 
-static hl_status lt_handle(hipblasLtHandle_t* out) {
+static hl_status lt_handle(hipblasLtHandle_t* out, int* dev_out) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0) return HL_EHIP;
   if (dev >= kMaxDevices) return HL_EUNSUPPORTED;
@@ -3188,6 +3198,7 @@ static hl_status lt_handle(hipblasLtHandle_t* out) {
     return HL_EHIP;
   }
   *out = g_lt[dev];
+  *dev_out = dev;
   return HL_OK;
 }
 
@@ -3213,37 +3224,43 @@ struct LtGemm {
   // algorithm that divides the sums over blocks then says how much its
   // partial tiles take, while asked with no room it answers with the same
   // algorithm and a need of zero, and stores them past a null pointer
-  // (2605x22784 at 200 tokens: 28.9 MB). `deep`: look beyond the first answer
-  // (60 us of host time, against 2).
-  hl_status find(uint64_t rows, uint64_t cols, uint32_t tokens, bool deep) {
-    hl_status st = lt_handle(&h);
+  // (2605x22784 at 200 tokens: 28.9 MB). Looking through its answers takes
+  // up to milliseconds of host time, so the choice is kept for its size.
+  hl_status find(uint64_t rows, uint64_t cols, uint32_t tokens) {
+    int dev = 0;
+    hl_status st = lt_handle(&h, &dev);
     if (st != HL_OK) return st;
     const hipblasOperation_t ta = HIPBLAS_OP_T, tb = HIPBLAS_OP_N;
-    const uint64_t room = 1ull << 40;
-    constexpr int kDeep = 16;
-    hipblasLtMatmulHeuristicResult_t heur[kDeep];
-    hipblasLtMatmulPreference_t pref = nullptr;
-    st = HL_EHIP;
-    if (hipblasLtMatmulDescCreate(&op, HIPBLAS_COMPUTE_32F, HIP_R_32F) == HIPBLAS_STATUS_SUCCESS &&
-        hipblasLtMatmulDescSetAttribute(op, HIPBLASLT_MATMUL_DESC_TRANSA, &ta, sizeof(ta)) == HIPBLAS_STATUS_SUCCESS &&
-        hipblasLtMatmulDescSetAttribute(op, HIPBLASLT_MATMUL_DESC_TRANSB, &tb, sizeof(tb)) == HIPBLAS_STATUS_SUCCESS &&
-        hipblasLtMatrixLayoutCreate(&la, HIP_R_16BF, cols, rows, (int64_t)cols) == HIPBLAS_STATUS_SUCCESS &&
-        hipblasLtMatrixLayoutCreate(&lb, HIP_R_16BF, cols, tokens, (int64_t)cols) == HIPBLAS_STATUS_SUCCESS &&
-        hipblasLtMatrixLayoutCreate(&ld, HIP_R_32F, rows, tokens, (int64_t)rows) == HIPBLAS_STATUS_SUCCESS &&
-        hipblasLtMatmulPreferenceCreate(&pref) == HIPBLAS_STATUS_SUCCESS &&
-        hipblasLtMatmulPreferenceSetAttribute(pref, HIPBLASLT_MATMUL_PREF_MAX_WORKSPACE_BYTES, &room,
-                                              sizeof(room)) == HIPBLAS_STATUS_SUCCESS) {
-      st = HL_EUNSUPPORTED;
-      for (int ask = 1; st != HL_OK && ask <= (deep ? kDeep : 1); ask += kDeep - 1) {
-        int found = 0;
-        if (hipblasLtMatmulAlgoGetHeuristic(h, op, la, lb, ld, ld, pref, ask, heur, &found) != HIPBLAS_STATUS_SUCCESS)
-          break;
-        for (int k = 0; k < std::min(found, ask) && st != HL_OK; ++k)
-          if (heur[k].workspaceSize == 0) algo = heur[k].algo, st = HL_OK;
+    if (hipblasLtMatmulDescCreate(&op, HIPBLAS_COMPUTE_32F, HIP_R_32F) != HIPBLAS_STATUS_SUCCESS ||
+        hipblasLtMatmulDescSetAttribute(op, HIPBLASLT_MATMUL_DESC_TRANSA, &ta, sizeof(ta)) != HIPBLAS_STATUS_SUCCESS ||
+        hipblasLtMatmulDescSetAttribute(op, HIPBLASLT_MATMUL_DESC_TRANSB, &tb, sizeof(tb)) != HIPBLAS_STATUS_SUCCESS ||
+        hipblasLtMatrixLayoutCreate(&la, HIP_R_16BF, cols, rows, (int64_t)cols) != HIPBLAS_STATUS_SUCCESS ||
+        hipblasLtMatrixLayoutCreate(&lb, HIP_R_16BF, cols, tokens, (int64_t)cols) != HIPBLAS_STATUS_SUCCESS ||
+        hipblasLtMatrixLayoutCreate(&ld, HIP_R_32F, rows, tokens, (int64_t)rows) != HIPBLAS_STATUS_SUCCESS)
+      return HL_EHIP;
+    std::lock_guard<std::mutex> lock(g_lt_mu);
+    for (const LtChoice& c : g_lt_choice[dev])
+      if (c.tokens == tokens && c.rows == rows && c.cols == cols) {
+        algo = c.algo;
+        return c.found ? HL_OK : HL_EUNSUPPORTED;
       }
-    }
+    const uint64_t room = 1ull << 40;
+    constexpr int kAsk = 16;
+    hipblasLtMatmulHeuristicResult_t heur[kAsk];
+    hipblasLtMatmulPreference_t pref = nullptr;
+    int found = 0;
+    const bool asked =
+        hipblasLtMatmulPreferenceCreate(&pref) == HIPBLAS_STATUS_SUCCESS &&
+        hipblasLtMatmulPreferenceSetAttribute(pref, HIPBLASLT_MATMUL_PREF_MAX_WORKSPACE_BYTES, &room, sizeof(room)) ==
+            HIPBLAS_STATUS_SUCCESS &&
+        hipblasLtMatmulAlgoGetHeuristic(h, op, la, lb, ld, ld, pref, kAsk, heur, &found) == HIPBLAS_STATUS_SUCCESS;
     if (pref) hipblasLtMatmulPreferenceDestroy(pref);
-    return st;
+    LtChoice c = {rows, cols, tokens, false, {}};
+    for (int k = 0; asked && k < std::min(found, kAsk) && !c.found; ++k)
+      if (heur[k].workspaceSize == 0) c.algo = heur[k].algo, c.found = true;
+    g_lt_choice[dev][g_lt_next[dev]++ % kLtChoices] = c;
+    algo = c.algo;
+    return c.found ? HL_OK : HL_EUNSUPPORTED;
   }
 
   hl_status run(const uint16_t* w, const uint16_t* x, float* y, hipStream_t stream) {
@@ -3325,10 +3342,9 @@ extern "C" hl_status hl_decode_gemm(const hl_tensor* t, const void* x_dev, hl_dt
   if (tokens > kGemmFusedMaxTokens) {
     // many tokens: decode once (bit-exact bf16 in the workspace), then the
     // GEMM; the fused kernel where the library has none without a workspace
-    // (few output tiles and long sums). One chunk of tokens decodes the
-    // matrix once there as well, so only more than that is worth a deep look.
+    // (few output tiles and long sums)
     LtGemm lt;
-    hl_status st = lt.find(t->rows, t->cols, tokens, tokens > kGemmMaxTiles * kTile);
+    hl_status st = lt.find(t->rows, t->cols, tokens);
     if (st == HL_OK) {
       uint16_t* w = reinterpret_cast<uint16_t*>(workspace_dev);
       st = hl_decode(t, w, stream);

@@ -1,8 +1,7 @@
 """Prefill products of more than 64 tokens whose vendor algorithm would divide
 the sums over blocks (few output tiles, long sums): they run without a GEMM
-workspace, by another algorithm (over 128 tokens) or the fused kernel, whose
-partial sums fit the workspace. Every output within the float32 rounding of a
-sum of cols products of the float64 value."""
+workspace, by another algorithm or the fused kernel, whose partial
+sums fit the workspace. Every output within the float32 rounding of a sum of cols products of the float64 value."""
 import numpy as np
 import pytest
 
