@@ -193,6 +193,16 @@ __global__ void __launch_bounds__(256) lut8_kernel(uint32_t* lut, Aux8 a) {
   for (int i = threadIdx.x; i < kAuxWords; i += blockDim.x) lut[kLutN + i] = 0;
 }
 
+// Bounded pairs (every weight's codes fit 11 bits, see bp_decode8) in the
+// matrix-core kernels of small matrices: the joint table's first 2048 entries once, in an
+// array of their own, so that a block copies and holds 8 KB instead of 33 and
+// its decode has no escapes (1000x4096 at batch 3: 11.6 us with the joint
+// table, 10.4 us; the replicated copies of the persistent kernel cost a
+// small block more than their bank conflicts).
+constexpr int kBpBits = HL_PAIR_MAX;
+constexpr uint32_t kBpN = 1u << kBpBits;
+__shared__ __attribute__((aligned(16))) uint32_t s_one[kBpN];
+
 // Copies the joint table and the aux tables into LDS, four 16-byte loads in
 // flight per thread.
 __device__ inline void load_tables(const uint32_t* lut) {
@@ -258,10 +268,13 @@ __device__ inline void dma4(const void* src, uint32_t* lds_base) {
   __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)lds_base, 4, 0, 0);
 }
 
+template <bool ONE>
 __device__ inline void table_dma(const uint32_t* lut) {
+  constexpr uint32_t kVec = ONE ? kBpN / 4 : kTabVec;
+  uint32_t* dst = ONE ? s_one : s_tab;
   const uint32_t n = blockDim.x, w0 = threadIdx.x & ~63u, lane = threadIdx.x & 63;
-  for (uint32_t k0 = w0; k0 < kTabVec; k0 += n)
-    if (k0 + lane < kTabVec) dma16(lut + (k0 + lane) * 4, s_tab + k0 * 4);
+  for (uint32_t k0 = w0; k0 < kVec; k0 += n)
+    if (k0 + lane < kVec) dma16(lut + (k0 + lane) * 4, dst + k0 * 4);
 }
 
 // ---- stream columns
@@ -475,12 +488,7 @@ __device__ inline void decode8(const uint32_t* sc, uint32_t sc_off, uint32_t jma
 // Positions here are column bit positions minus 5: the window's low 16 bits
 // then hold five old bits and the 11-bit index already scaled by 32, the
 // byte offset of the entry's first copy.
-#ifndef HL_BP_BITS
-#define HL_BP_BITS HL_PAIR_MAX
-#endif
-constexpr int kBpBits = HL_BP_BITS;
-static_assert(kBpBits <= (int)HL_PAIR_MAX && kBpBits >= 9, "table window");
-constexpr uint32_t kBpN = 1u << kBpBits;
+static_assert(kBpBits >= 9, "table window");
 constexpr uint32_t kBpCopies = 1u << (14 - kBpBits);
 constexpr uint32_t kBpShift = 16 - kBpBits;  // log2 of an entry's bytes over all copies
 constexpr uint32_t kBpWords = kBpN * kBpCopies;  // 64 KB
@@ -518,21 +526,25 @@ __device__ inline void bp_table_store(const uint32_t (&te)[kBpPerThread]) {
   }
 }
 
+template <bool ONE>
 __device__ inline uint32_t bp_at(uint32_t w, uint32_t lane_off) {
+  if constexpr (ONE)
+    return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(s_one) + (w & ((kBpN - 1) << 2)));
   const uint32_t off = (w & ((kBpN - 1) << kBpShift)) | lane_off;
   return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(s_bp) + off);
 }
 
 // Four table reads from the window W, shifted past each pair read (W ends
 // shifted past all four).
+template <bool ONE>
 __device__ inline void bp_lookup4(uint64_t& W, uint32_t* e, uint32_t lane_off) {
-  e[0] = bp_at((uint32_t)W, lane_off);
+  e[0] = bp_at<ONE>((uint32_t)W, lane_off);
   W = shift_window(W, e[0]);
-  e[1] = bp_at((uint32_t)W, lane_off);
+  e[1] = bp_at<ONE>((uint32_t)W, lane_off);
   W = shift_window(W, e[1]);
-  e[2] = bp_at((uint32_t)W, lane_off);
+  e[2] = bp_at<ONE>((uint32_t)W, lane_off);
   W = shift_window(W, e[2]);
-  e[3] = bp_at((uint32_t)W, lane_off);
+  e[3] = bp_at<ONE>((uint32_t)W, lane_off);
 }
 
 // decode8 for bounded pairs: no branch. The first window is bits [p, p + 64)
@@ -544,6 +556,9 @@ __device__ inline void bp_lookup4(uint64_t& W, uint32_t* e, uint32_t lane_off) {
 // and then every window reads one and the same entry, so the refill's place
 // does not matter.) jmax - 1
 // bounds the first of the four rows read (columns hold three rows of overrun).
+// ONE: the single copy of the table, whose positions are minus 2 as the joint
+// table's (even more of the second window is then new).
+template <bool ONE>
 __device__ inline void bp_decode8(const uint32_t* sc, uint32_t jmax, uint32_t& pos5, uint32_t* e,
                                   uint32_t lane_off) {
   const uint32_t p = pos5;
@@ -551,12 +566,19 @@ __device__ inline void bp_decode8(const uint32_t* sc, uint32_t jmax, uint32_t& p
   const uint32_t w0 = col_word(sc, j), w1 = col_word(sc, j + 1), w2 = col_word(sc, j + 2), w3 = col_word(sc, j + 3);
   uint64_t W = funnel64(w2, w1, w0, p);
   const uint32_t t = __builtin_amdgcn_alignbit(w3, w2, p);
-  bp_lookup4(W, e, lane_off);
+  bp_lookup4<ONE>(W, e, lane_off);
   W = shift_window(W, e[3]);
   const uint32_t p4 = p + e[0] + e[1] + e[2] + e[3];
   W |= (uint64_t)t << ((p - p4) & 63u);  // 64 - (bits of the four pairs)
-  bp_lookup4(W, e + 4, lane_off);
+  bp_lookup4<ONE>(W, e + 4, lane_off);
   pos5 = p4 + e[4] + e[5] + e[6] + e[7];
+}
+
+// Eight weights in the matrix-core kernels of small matrices: by the single
+// bounded-pair table (ONE) or the joint table.
+template <bool ONE>
+__device__ inline void small_decode8(const uint32_t* sc, uint32_t sc_off, uint32_t jmax, uint32_t& pos2, uint32_t* e) {
+  if constexpr (ONE) bp_decode8<true>(sc, jmax, pos2, e, 0); else decode8(sc, sc_off, jmax, pos2, e);
 }
 
 // Packed bf16 pair (weights k, k+1 of a raw dword) from two table entries.
@@ -1070,7 +1092,7 @@ __device__ inline void mfma_finish(const GemvArgs& p, const f32x4_t& acc, float*
 // are read straight into registers, KP steps ahead of their use, the last
 // chunk of a group prefetching the next group's first chunk. SP = S/8 steps
 // per group, unrolled so that every wait on a prefetch is exact.
-template <int SP, bool XT>
+template <int SP, bool XT, bool ONE>
 __global__ void __launch_bounds__(1024) gemv_mfma_kernel(GemvArgs p) {
   constexpr int KP = SP < 8 ? SP : SP == 8 ? 8 : 4;  // 16 steps at depth 8 exceed 128 VGPRs
   const GroupArgs& a = p.g;
@@ -1109,7 +1131,7 @@ __global__ void __launch_bounds__(1024) gemv_mfma_kernel(GemvArgs p) {
   const uint32_t cb0 = min(cb, a.CB - 1);
   Meta m = load_meta(a, rb * a.CB + cb0, lane);
   Meta mn = load_meta(a, rb * a.CB + (cb + waves < cb_end ? cb + waves : cb0), lane);
-  table_dma(a.lut);
+  table_dma<ONE>(a.lut);
   uint32_t pos2 = issue_stream(a, cols, m, lane);
   uint2 rw[KP];
   uint4 xv[KP];
@@ -1153,7 +1175,7 @@ __global__ void __launch_bounds__(1024) gemv_mfma_kernel(GemvArgs p) {
 #pragma unroll
       for (int k = 0; k < KP; ++k) {
         uint32_t e[8];
-        decode8(sc, sc_off, jmax, pd, e);
+        small_decode8<ONE>(sc, sc_off, jmax, pd, e);
         uint4 wv;
         wv.x = pack_pair(rw[k].x, 0, e[0], e[1]);
         wv.y = pack_pair(rw[k].x, 2, e[2], e[3]);
@@ -1214,7 +1236,7 @@ __device__ inline uint32_t xslice_offset(uint32_t row, uint32_t chunk) {
 // one range (KS = 1) the block writes Y; otherwise it writes its partial sums
 // and gemm_reduce_kernel adds the ranges in order (results do not vary
 // between runs).
-template <int SP, int NT>
+template <int SP, int NT, bool ONE>
 __global__ void __launch_bounds__(1024) gemm_mfma_kernel(GemmArgs p) {
   constexpr uint32_t S = SP * 8;
   constexpr uint32_t kChunks = 4 * S / 8;       // 16-byte chunks per token row
@@ -1258,7 +1280,7 @@ __global__ void __launch_bounds__(1024) gemm_mfma_kernel(GemmArgs p) {
       for (int k = 0; k < SP; ++k) rw[k] = *reinterpret_cast<const uint2*>(r + k * rstride);
     }
     asm volatile("" : "+v"(m.nbw), "+v"(m.u0)::"memory");
-    if (cb == kb0) table_dma(a.lut);
+    if (cb == kb0) table_dma<ONE>(a.lut);
     const uint32_t pos2 = issue_stream(a, cols, m, lane);
     // Copy k of a wave fills the 1 KB at k*1024 of the slice; its lane L
     // writes position L there and so loads the chunk that the swizzle puts
@@ -1277,7 +1299,7 @@ __global__ void __launch_bounds__(1024) gemm_mfma_kernel(GemmArgs p) {
 #pragma unroll
     for (int k = 0; k < SP; ++k) {
       uint32_t e[8];
-      decode8(sc, sc_off, jmax, pd, e);
+      small_decode8<ONE>(sc, sc_off, jmax, pd, e);
       uint4 wv;
       wv.x = pack_pair(rw[k].x, 0, e[0], e[1]);
       wv.y = pack_pair(rw[k].x, 2, e[2], e[3]);
@@ -1931,7 +1953,7 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
   uint32_t te[kBpPerThread];
   if constexpr (BP) bp_table_load(a.lut, te);
   else if constexpr (F16) table16_dma(a);
-  else table_dma(a.lut);
+  else table_dma<false>(a.lut);
   Meta m0 = load_meta(a, g0, lane);
   Meta m1 = load_meta(a, g1, lane);
   if constexpr (BP) bp_table_store(te);
@@ -2032,7 +2054,7 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
           wv = pack8_f16(h, sg.byte(k));
         } else {
           uint32_t e[8];
-          if constexpr (BP) bp_decode8(sc, jmax, pd, e, lane_off); else decode8(sc, sc_off, jmax, pd, e);
+          if constexpr (BP) bp_decode8<false>(sc, jmax, pd, e, lane_off); else decode8(sc, sc_off, jmax, pd, e);
           wv.x = pack_pair(rw[k].x, 0, e[0], e[1]);
           wv.y = pack_pair(rw[k].x, 2, e[2], e[3]);
           wv.z = pack_pair(rw[k].y, 0, e[4], e[5]);
@@ -2277,11 +2299,27 @@ static bool allow_lds(const void* kernel, size_t lds) {
   }
 }
 
+// Longest code of a weight's exponent (the pair of the split format, the one
+// code of the whole-exponent format), over the symbols present.
+static uint32_t longest_exponent_code(const hl_tensor* t) {
+  uint32_t a = 0, b = 0;
+  if (t->format == HL_FORMAT_SPLIT) {
+    for (int k = 0; k < 16; ++k) a = std::max<uint32_t>(a, t->cb.eh.len[k]), b = std::max<uint32_t>(b, t->cb.el.len[k]);
+  } else if (t->format == HL_FORMAT_WHOLE_EXPONENT) {
+    for (int k = 0; k < 256; ++k) a = std::max<uint32_t>(a, t->cb8.len[k]);
+  } else {
+    return 99;
+  }
+  return a + b;
+}
+
 struct Plan {
   GroupArgs ga;
+  bool one;           // the single bounded-pair table (matrix-core kernels of small matrices)
   uint32_t waves;
   size_t lds;       // dynamic LDS: (float16 tables) + the wave regions
   size_t tab_dyn;   // bytes of the float16 tables in it
+  size_t tab_static;  // bytes of the bf16 formats' table
   size_t wave_bytes;  // bytes of one wave region
   // dynamic LDS of a block of w waves
   size_t lds_for(uint32_t w) const { return tab_dyn + (size_t)w * wave_bytes; }
@@ -2330,7 +2368,9 @@ static hl_status make_plan(const hl_tensor* t, uint32_t extra_words_per_wave, bo
     a.t16_aux = lay.aux;
     a.t16_words = lay.words;
   }
-  const size_t tab_static = is_fp16(t) ? 0 : (size_t)(kLutN + kAuxWords) * 4;
+  pl->one = !raw_lds && longest_exponent_code(t) <= (uint32_t)kBpBits;
+  const size_t tab_static = is_fp16(t) ? 0 : (size_t)(pl->one ? kBpN : kLutN + kAuxWords) * 4;
+  pl->tab_static = tab_static;
   const size_t tab_dyn = is_fp16(t) ? (size_t)a.t16_words * 4 : 0;
   uint32_t waves = kMaxWaves;
   while (waves > 1 && tab_static + tab_dyn + (size_t)waves * per_wave * 4 > kMaxLds) --waves;
@@ -2524,22 +2564,26 @@ static bool mfma_steps_ok(uint32_t steps) {
   return steps == 1 || steps == 2 || steps == 4 || steps == 8 || steps == 16;
 }
 
-template <bool XT>
+template <bool XT, bool ONE>
 static hl_status launch_mfma_x(uint32_t steps, dim3 grid, dim3 block, size_t lds, hipStream_t s,
                                const GemvArgs& p) {
   switch (steps) {
-    case 1: return launch(gemv_mfma_kernel<1, XT>, grid, block, lds, s, p);
-    case 2: return launch(gemv_mfma_kernel<2, XT>, grid, block, lds, s, p);
-    case 4: return launch(gemv_mfma_kernel<4, XT>, grid, block, lds, s, p);
-    case 8: return launch(gemv_mfma_kernel<8, XT>, grid, block, lds, s, p);
-    case 16: return launch(gemv_mfma_kernel<16, XT>, grid, block, lds, s, p);
+    case 1: return launch(gemv_mfma_kernel<1, XT, ONE>, grid, block, lds, s, p);
+    case 2: return launch(gemv_mfma_kernel<2, XT, ONE>, grid, block, lds, s, p);
+    case 4: return launch(gemv_mfma_kernel<4, XT, ONE>, grid, block, lds, s, p);
+    case 8: return launch(gemv_mfma_kernel<8, XT, ONE>, grid, block, lds, s, p);
+    case 16: return launch(gemv_mfma_kernel<16, XT, ONE>, grid, block, lds, s, p);
     default: return HL_EUNSUPPORTED;
   }
 }
 
-static hl_status launch_mfma(bool xt, uint32_t steps, dim3 grid, dim3 block, size_t lds, hipStream_t s,
+static hl_status launch_mfma(bool xt, bool one, uint32_t steps, dim3 grid, dim3 block, size_t lds, hipStream_t s,
                              const GemvArgs& p) {
-  return xt ? launch_mfma_x<true>(steps, grid, block, lds, s, p) : launch_mfma_x<false>(steps, grid, block, lds, s, p);
+  if (one)
+    return xt ? launch_mfma_x<true, true>(steps, grid, block, lds, s, p)
+              : launch_mfma_x<false, true>(steps, grid, block, lds, s, p);
+  return xt ? launch_mfma_x<true, false>(steps, grid, block, lds, s, p)
+            : launch_mfma_x<false, false>(steps, grid, block, lds, s, p);
 }
 
 template <int B>
@@ -2637,20 +2681,6 @@ extern "C" hl_status hl_tensor_prepare(const hl_tensor* t, void* stream) {
 // matrix does not fit it (16-row groups of the bf16 formats at S = 32 or 64,
 // at least one row block per CU and two groups per wave of at least 8 waves
 // per block, every segment within the largest stream word count).
-// Longest code of a weight's exponent (the pair of the split format, the one
-// code of the whole-exponent format), over the symbols present.
-static uint32_t longest_exponent_code(const hl_tensor* t) {
-  uint32_t a = 0, b = 0;
-  if (t->format == HL_FORMAT_SPLIT) {
-    for (int k = 0; k < 16; ++k) a = std::max<uint32_t>(a, t->cb.eh.len[k]), b = std::max<uint32_t>(b, t->cb.el.len[k]);
-  } else if (t->format == HL_FORMAT_WHOLE_EXPONENT) {
-    for (int k = 0; k < 256; ++k) a = std::max<uint32_t>(a, t->cb8.len[k]);
-  } else {
-    return 99;
-  }
-  return a + b;
-}
-
 // The persistent kernel's bounded-pair form applies (S = 64, pairs within
 // the 11-bit window).
 static bool bounded_pairs(const hl_tensor* t) {
@@ -2725,7 +2755,7 @@ extern "C" hl_status hl_decode(const hl_tensor* t, uint16_t* out_dev, void* stre
                                      (hipStream_t)stream, pl.ga, out_dev);
   }
   const uint32_t per_cu =
-      std::max<uint32_t>(1, std::min<uint32_t>(8, kMaxLds / (uint32_t)(pl.lds + (kLutN + kAuxWords) * 4)));
+      std::max<uint32_t>(1, std::min<uint32_t>(8, kMaxLds / (uint32_t)(pl.lds + pl.tab_static)));
   const uint32_t blocks = std::min<uint32_t>((n_grp + pl.waves - 1) / pl.waves, device_cus() * per_cu);
   return launch(decode_kernel, dim3(blocks), dim3(pl.waves * 64), pl.lds, (hipStream_t)stream, pl.ga,
                 out_dev);
@@ -2993,7 +3023,7 @@ static hl_status gemv_impl(const hl_tensor* t, const void* x_dev, hl_dtype x_dty
   if (mfma) {
     // the reduction reuses the wave regions: 4 floats per lane per wave
     const size_t lds = std::max<size_t>(pl.lds_for(w), (size_t)w * 4 * 64 * 4);
-    return launch_mfma(xt, t->seg_len / 8, grid, block, lds, stream, p);
+    return launch_mfma(xt, pl.one, t->seg_len / 8, grid, block, lds, stream, p);
   }
   const size_t lds = std::max<size_t>(pl.lds_for(w), (size_t)w * batch * 64 * 4);
   HL_BATCH_SWITCH(launch_gemv_b, batch, xb, grid, block, lds, stream, p);
@@ -3272,13 +3302,13 @@ struct LtGemm {
   }
 };
 
-template <int SP>
+template <int SP, bool ONE>
 static hl_status launch_gemm_sp(uint32_t nt, dim3 grid, size_t lds, hipStream_t s, const GemmArgs& p) {
   switch (nt) {
-    case 1: return launch(gemm_mfma_kernel<SP, 1>, grid, dim3(1024), lds, s, p);
-    case 2: return launch(gemm_mfma_kernel<SP, 2>, grid, dim3(1024), lds, s, p);
-    case 4: return launch(gemm_mfma_kernel<SP, 4>, grid, dim3(1024), lds, s, p);
-    case 8: return launch(gemm_mfma_kernel<SP, 8>, grid, dim3(1024), lds, s, p);
+    case 1: return launch(gemm_mfma_kernel<SP, 1, ONE>, grid, dim3(1024), lds, s, p);
+    case 2: return launch(gemm_mfma_kernel<SP, 2, ONE>, grid, dim3(1024), lds, s, p);
+    case 4: return launch(gemm_mfma_kernel<SP, 4, ONE>, grid, dim3(1024), lds, s, p);
+    case 8: return launch(gemm_mfma_kernel<SP, 8, ONE>, grid, dim3(1024), lds, s, p);
     default: return HL_EUNSUPPORTED;
   }
 }
@@ -3360,7 +3390,7 @@ extern "C" hl_status hl_decode_gemm(const hl_tensor* t, const void* x_dev, hl_dt
   // Token tiles per block: as many as the tokens need (a power of two, at
   // most 8) and the LDS holds next to 16 waves' stream columns and the table.
   const size_t cols_bytes = (size_t)16 * pl.ga.col_rows * kCol * 4;
-  const size_t tab = (size_t)(kLutN + kAuxWords) * 4;
+  const size_t tab = pl.tab_static;
   uint32_t nt = 1;
   while (nt < kGemmMaxTiles && nt * 16 < tokens) nt *= 2;
   while (nt > 1 && tab + (size_t)nt * SP * 1024 + cols_bytes > kMaxLds) nt /= 2;
@@ -3389,8 +3419,12 @@ extern "C" hl_status hl_decode_gemm(const hl_tensor* t, const void* x_dev, hl_dt
   const uint64_t blocks = (uint64_t)p.KS * base;
   if (blocks >= (1ull << 31)) return HL_EUNSUPPORTED;
   const size_t lds = slice + cols_bytes;
-  st = SP == 8 ? launch_gemm_sp<8>(nt, dim3((uint32_t)blocks), lds, (hipStream_t)stream, p)
-               : launch_gemm_sp<4>(nt, dim3((uint32_t)blocks), lds, (hipStream_t)stream, p);
+  const dim3 grid((uint32_t)blocks);
+  const hipStream_t hs = (hipStream_t)stream;
+  if (pl.one)
+    st = SP == 8 ? launch_gemm_sp<8, true>(nt, grid, lds, hs, p) : launch_gemm_sp<4, true>(nt, grid, lds, hs, p);
+  else
+    st = SP == 8 ? launch_gemm_sp<8, false>(nt, grid, lds, hs, p) : launch_gemm_sp<4, false>(nt, grid, lds, hs, p);
   if (st != HL_OK || p.KS == 1) return st;
   const uint64_t n = (uint64_t)tokens * t->rows;
   const uint32_t rblocks = (uint32_t)std::min<uint64_t>((n + 255) / 256, (uint64_t)device_cus() * 8);
