@@ -197,7 +197,7 @@ __global__ void __launch_bounds__(256) lut8_kernel(uint32_t* lut, Aux8 a) {
 // matrix-core kernels of small matrices: the joint table's first 2048 entries once, in an
 // array of their own, so that a block copies and holds 8 KB instead of 33 and
 // its decode has no escapes (1000x4096 at batch 3: 11.6 us with the joint
-// table, 10.4 us; the replicated copies of the persistent kernel cost a
+// table, 10.4 us with this one; the replicated copies of the persistent kernel cost a
 // small block more than their bank conflicts).
 constexpr int kBpBits = HL_PAIR_MAX;
 constexpr uint32_t kBpN = 1u << kBpBits;
@@ -1872,8 +1872,12 @@ __device__ inline const GemvArgs& gemv_args(const Args& x) {
 // weights until its stores, or with several tiles; 12 for the float16
 // product, whose longer stream columns need more registers).
 constexpr uint32_t stream_threads(bool dec, int tb, int nt = 1) {
-  return dec || nt > 1 ? 512 : tb == 2 ? 768 : 1024;
+  return dec ? 512 : nt == 4 ? 768 : tb == 2 ? 768 : 1024;
 }
+// Steps that activations are loaded ahead of their product: a whole group
+// (its registers: 4 SP NT), or with several tiles as many as leave registers
+// for these blocks.
+constexpr int stream_ahead(int sp, int nt) { return nt == 4 ? 2 : nt == 2 ? 4 : sp; }
 
 template <int SP, int JT, bool XT, class Args, bool DEC, int TB, int NT = 1>
 __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kernel(Args sa) {
@@ -1961,8 +1965,10 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
   uint32_t pos2 = stream_load<JT>(a, m0, lane, sw) - kOld;
   uint2 rw[F16 ? 1 : SP];  // raw bytes of the next group's steps (bf16 formats)
   Signs<SP> sg, sgn;       // float16: the lane's sign bytes of this and the next group
-  uint4 xv[SP];
-  uint4 xe[NE][SP];  // the other tiles' activations
+  constexpr int XD = stream_ahead(SP, NT);
+  static_assert(SP % XD == 0, "the next group's activations fall in the same registers");
+  uint4 xv[XD];
+  uint4 xe[NE][XD];  // the other tiles' activations
   // raw bytes of the first group's first half of the steps with its stream
   // words, the second half once those are in: every wave requests its first
   // group at once, and a wave's stream words would otherwise queue behind
@@ -1977,10 +1983,11 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
 #pragma unroll
     for (int k = 0; k < SP; ++k) {
       if constexpr (!F16) if (k < kEarlyRaw) rw[k] = *reinterpret_cast<const uint2*>(raw0 + k * G * 32u);
-      if constexpr (!DEC) xv[k] = *reinterpret_cast<const uint4*>(xbytes + m0.c0 * XSEG + xoff + k * XSTEP);
+      if constexpr (!DEC)
+        if (k < XD) xv[k] = *reinterpret_cast<const uint4*>(xbytes + m0.c0 * XSEG + xoff + k * XSTEP);
 #pragma unroll
       for (int u = 1; u < NT; ++u)
-        xe[u - 1][k] = *reinterpret_cast<const uint4*>(xbytes + m0.c0 * XSEG + xoff + 256u * u + k * XSTEP);
+        if (k < XD) xe[u - 1][k] = *reinterpret_cast<const uint4*>(xbytes + m0.c0 * XSEG + xoff + 256u * u + k * XSTEP);
     }
     if constexpr (NT == 4) {
       // a precaution: no scalar write into these loads' scalar base right
@@ -1995,7 +2002,7 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
   stream_store<JT>(cols, sw, lane);
   // everything but the raw (or sign) and activation loads
   constexpr int kRawLoads = F16 ? 1 : kEarlyRaw;
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(kRawLoads + (DEC ? 0 : SP * NT)));
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(kRawLoads + (DEC ? 0 : XD * NT)));
   asm volatile("" ::: "memory");
   if constexpr (!F16) {
     const uint32_t G = min(16u, a.rows - (g0 / CB) * 16);
@@ -2040,6 +2047,7 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
       const uint32_t roff = okn ? lane_mu(rbn) * 8 : DEC ? mu * 8 : xoff;
       const uint32_t rs = okn ? Gn * 32u : 0u;
       const uint8_t* xbase = xbytes + (okn ? n_c0 : cur_c0) * XSEG;
+      const uint8_t* xcur = xbytes + cur_c0 * XSEG;
       uint32_t pd = (uint32_t)__shfl((int)pos2, (int)mu, 64);
       uint4 dv[DEC ? SP : 1];  // decoding: the lane's weights of the group
       // float16: the next group's sign bytes (after the wave's last group of
@@ -2065,10 +2073,10 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
         } else {
           if constexpr (F16)
             acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, wv),
-                                                         __builtin_bit_cast(f16x8_t, xv[k]), acc, 0, 0, 0);
+                                                         __builtin_bit_cast(f16x8_t, xv[k % XD]), acc, 0, 0, 0);
           else if constexpr (NT == 1)
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wv),
-                                                          __builtin_bit_cast(bf16x8_t, xv[k]), acc, 0, 0, 0);
+                                                          __builtin_bit_cast(bf16x8_t, xv[k % XD]), acc, 0, 0, 0);
           if constexpr (NT == 1) {
             mfma_operand_guard();
           } else {
@@ -2079,14 +2087,14 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
             // came right after)
             __builtin_amdgcn_sched_barrier(0);
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wv),
-                                                          __builtin_bit_cast(bf16x8_t, xv[k]), acc, 0, 0, 0);
+                                                          __builtin_bit_cast(bf16x8_t, xv[k % XD]), acc, 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             mfma_operand_guard();
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int u = 0; u < NT - 1; ++u) {
               acce[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wv),
-                                                                __builtin_bit_cast(bf16x8_t, xe[u][k]), acce[u], 0, 0,
+                                                                __builtin_bit_cast(bf16x8_t, xe[u][k % XD]), acce[u], 0, 0,
                                                                 0);
               __builtin_amdgcn_sched_barrier(0);
               mfma_operand_guard();
@@ -2094,10 +2102,10 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
             }
           }
           // x first: the wait for the raw bytes at their use then covers both
-          xv[k] = *reinterpret_cast<const uint4*>(xbase + xoff + k * XSTEP);
+          const uint8_t* xp = k + XD < SP ? xcur + (k + XD) * XSTEP : xbase + (k + XD - SP) * XSTEP;
+          xv[k % XD] = *reinterpret_cast<const uint4*>(xp + xoff);
 #pragma unroll
-          for (int u = 1; u < NT; ++u)
-            xe[u - 1][k] = *reinterpret_cast<const uint4*>(xbase + xoff + 256u * u + k * XSTEP);
+          for (int u = 1; u < NT; ++u) xe[u - 1][k % XD] = *reinterpret_cast<const uint4*>(xp + xoff + 256u * u);
         }
         if constexpr (F16) {
           if (k == 0) sgn.load(sgnext);
@@ -2181,7 +2189,7 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
           if (i < p.B && 4 * q + v < G) yp[(uint64_t)i * a.rows + rb * 16 + 4 * q + v] = sum;
         }
       } else {
-        // wave u % waves sums piece v = u % 4 of tile u / 4 (blocks of 8 waves)
+        // wave u % waves sums piece v = u % 4 of tile u / 4
         for (uint32_t u = wave; u < 4u * NT; u += waves) {
           const uint32_t v = u & 3, tile = u >> 2, n = tile * 16 + i;
           float sum = 0.f;
@@ -2478,8 +2486,9 @@ static hl_status launch_stream_tiles_tb(uint32_t seg_len, int jt, dim3 grid, dim
 
 static hl_status launch_stream_tiles(int nt, bool bp, uint32_t seg_len, int jt, dim3 grid, dim3 block, size_t lds,
                                      hipStream_t s, const GemvArgs& g) {
-  // eight waves: every tile's sums at the row-block end
-  if (!tiles_supported(nt, seg_len, jt) || block.x != stream_threads(false, bp ? 1 : 0, nt)) return HL_EINVAL;
+  if (!tiles_supported(nt, seg_len, jt) || block.x > stream_threads(false, bp ? 1 : 0, nt) ||
+      block.x < kBpMinThreads)
+    return HL_EINVAL;
   if (nt == 4)
     return bp ? launch_stream_tiles_tb<1, 4>(seg_len, jt, grid, block, lds, s, g)
               : launch_stream_tiles_tb<0, 4>(seg_len, jt, grid, block, lds, s, g);
@@ -3354,7 +3363,7 @@ extern "C" hl_status hl_decode_gemm(const hl_tensor* t, const void* x_dev, hl_dt
                      : launch(xtile_kernel<4 * kTile>, tgrid, dim3(256), 0, (hipStream_t)stream, xs, tokens, chunks, tile);
         if (sp != HL_OK) return sp;
         p.x = tile;
-        w = stream_threads(false, bp ? 1 : 0, nt) / 64;
+        w = std::min<uint32_t>(w, stream_threads(false, bp ? 1 : 0, nt) / 64);
         return launch_stream_tiles(nt, bp, t->seg_len, jt, grid, dim3(w * 64), w * per_wave, (hipStream_t)stream, p);
       }
       bool xt = false;
