@@ -2701,6 +2701,25 @@ static int stream_table(const hl_tensor* t) {
   return is_fp16(t) ? (flat_mh(t->cb16) ? 3 : 2) : bounded_pairs(t) ? 1 : 0;
 }
 
+// Waves per block of the persistent kernel: at most `most`, what the LDS
+// holds, and the column blocks (a 14336x2560 product of 10 waves takes 21.1
+// us, 29.5 on the non-persistent kernel; 20000x3840 31.8 and 51.2; decoding
+// them 38.8 and 62.1, 59.0 and 120.8); fewer when that gives every wave two
+// groups (the second group's loads then overlap the first one's decode). The
+// bf16 formats take no more than a row block's rounds need, in fours (one for
+// each SIMD): q, k and v of 4096 and twice 1024 rows by 4096 are 16 column
+// blocks, two rounds of 8 waves as of 12 (19.2 us, 20.7 with 12). Float16's
+// longer decode wants the waves (6700x4608 34.0 us with 14, 36.7 with 12).
+static uint32_t stream_waves(uint32_t most, size_t tab, size_t per_wave, uint32_t CB, uint64_t groups, uint32_t cus,
+                             int table) {
+  uint32_t w = std::min<uint32_t>(kMaxWaves, most);
+  if (table != 2) w = std::min(w, std::max<uint32_t>(CB, 1));
+  while (w > 1 && tab + w * per_wave > kMaxLds) --w;
+  while (w > 8 && groups < 2ull * cus * w) --w;
+  const uint32_t rounds = (CB + w - 1) / w;
+  return rounds > 1 && table < 2 ? std::min(w, ((CB + rounds - 1) / rounds + 3) & ~3u) : w;
+}
+
 static bool stream_shape(const hl_tensor* t, const GroupArgs& ga, int* jt, uint32_t* waves, size_t* per_wave) {
   if (t->grp_rows != 16 || (t->seg_len != 64 && t->seg_len != 32)) return false;
   const uint32_t CB = ga.CB, RB = ga.RB, cus = (uint32_t)device_cus();
@@ -2709,18 +2728,24 @@ static bool stream_shape(const hl_tensor* t, const GroupArgs& ga, int* jt, uint3
                      : bounded_pairs(t) ? (size_t)kBpWords * 4
                                         : (size_t)(kLutN + kAuxWords) * 4;
   *per_wave = (size_t)(*jt + 1) * kCol * 4;
-  uint32_t w = std::min<uint32_t>(kMaxWaves, stream_threads(false, stream_table(t)) / 64);
-  while (w > 1 && tab + w * *per_wave > kMaxLds) --w;
-  // fewer waves per block when that gives every wave two groups: the
-  // second group's loads then overlap the first one's decode
-  while (w > 8 && (uint64_t)RB * CB < 2ull * cus * w) --w;
+  const int table = stream_table(t);
+  const uint32_t w = stream_waves(stream_threads(false, table) / 64, tab, *per_wave, CB, (uint64_t)RB * CB, cus, table);
   *waves = w;
   // float16 without flat mh codes: two row blocks per CU at least (4096x4096,
   // one per CU: 25.9 us against 24.3 us on the non-persistent kernel;
   // 14336x4096 65.8 against 86.2 us). With them one is enough (4096x4096 20.2
   // against 20.3 us; decoding 4096x11008 55.8 against 98.8 us).
-  const uint32_t min_rb = stream_table(t) == 2 ? 2 * cus : cus;
+  const uint32_t min_rb = table == 2 ? 2 * cus : cus;
   return *jt && w >= 8 && CB >= w && RB >= min_rb && (uint64_t)RB * CB >= 2ull * cus * w;
+}
+
+// The same for a product: float16 matrices of 8 column blocks and many row
+// blocks stay on the non-persistent kernel, two 8-wave blocks on a CU
+// (28672x2048 53.3 us there, 61.9 us here; 28000x2304, 9 column blocks,
+// 95.0 and 68.9).
+static bool stream_product(const hl_tensor* t, const GroupArgs& ga, int* jt, uint32_t* waves, size_t* per_wave) {
+  if (is_fp16(t) && ga.CB == 8 && (uint64_t)ga.RB * ga.CB >= 18ull * device_cus()) return false;
+  return stream_shape(t, ga, jt, waves, per_wave);
 }
 
 extern "C" hl_status hl_decode(const hl_tensor* t, uint16_t* out_dev, void* stream) {
@@ -2902,7 +2927,7 @@ static hl_status gemv16(const hl_tensor* t, const void* x_dev, uint32_t batch, f
   uint32_t w = 0;
   size_t per_wave = 0;
   bool xt = false;
-  if (stream_shape(t, pl.ga, &jt, &w, &per_wave)) {
+  if (stream_product(t, pl.ga, &jt, &w, &per_wave)) {
     st = tile_activations(t, x_dev, batch, workspace_dev, workspace_bytes, stream, &p, &xt);
     if (st != HL_OK) return st;
     p.C = pl.ga.CB;
@@ -2935,7 +2960,7 @@ static hl_status gemv_plan(const hl_tensor* t, hl_dtype x_dtype, uint32_t batch,
   int jt = 0;
   uint32_t w = 0;
   size_t per_wave = 0;
-  *persistent = *mfma && stream_shape(t, pl->ga, &jt, &w, &per_wave);
+  *persistent = *mfma && stream_product(t, pl->ga, &jt, &w, &per_wave);
   return HL_OK;
 }
 
@@ -2948,7 +2973,7 @@ static uint64_t gemv_need(const hl_tensor* t, hl_dtype x_dtype, uint32_t batch) 
     int jt = 0;
     uint32_t w = 0;
     size_t per_wave = 0;
-    if (stream_shape(t, pl.ga, &jt, &w, &per_wave)) return xtile_region(t, batch);
+    if (stream_product(t, pl.ga, &jt, &w, &per_wave)) return xtile_region(t, batch);
   } else {
     bool mfma = false, persistent = false;
     uint32_t xw = 0;
@@ -3010,7 +3035,7 @@ static hl_status gemv_impl(const hl_tensor* t, const void* x_dev, hl_dtype x_dty
     int jt = 0;
     uint32_t w = 0;
     size_t per_wave = 0;
-    if (stream_shape(t, pl.ga, &jt, &w, &per_wave)) {
+    if (stream_product(t, pl.ga, &jt, &w, &per_wave)) {
       p.C = CB;
       p.KS = 1;
       StreamArgs sa;  // one matrix: only sa.p (with p.g, p.y) reaches the kernel
@@ -3117,9 +3142,7 @@ static bool group_shape(const hl_tensor* const* ts, uint32_t count, GroupShape* 
   for (uint32_t k = 0; k < count && g->bp; ++k) g->bp = bounded_pairs(ts[k]);
   const size_t tab = g->bp ? (size_t)kBpWords * 4 : (size_t)(kLutN + kAuxWords) * 4;
   g->per_wave = (size_t)(g->jt + 1) * kCol * 4;
-  uint32_t w = kMaxWaves;
-  while (w > 1 && tab + w * g->per_wave > kMaxLds) --w;
-  while (w > 8 && groups < 2ull * cus * w) --w;
+  const uint32_t w = stream_waves(kMaxWaves, tab, g->per_wave, g->pl[0].ga.CB, groups, cus, g->bp ? 1 : 0);
   if (!(w >= 8 && g->pl[0].ga.CB >= w && rbs >= cus)) return false;
   g->w = w;
   g->used = count;
