@@ -1930,14 +1930,26 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
 
   // the wave's groups in order: round t (row block bid + t*nblk of the
   // block's matrix), step j; branch-free (a branch between a load and its use
-  // makes the compiler's wait for it conservative)
+  // makes the compiler's wait for it conservative). Decoding, no sum ties a
+  // block to its row blocks: the waves of all blocks take the groups in turn
+  // (round t, j = 0), so that no block is left with a row block more than the
+  // others and no wave without a group at the end of each (5120x5120, 320 row
+  // blocks of 20 column blocks on 256 blocks of 8 waves: 31.5 us by row
+  // blocks, 26.2 us in turn). The last round's groups go to few waves of every
+  // block, which then decode faster, instead of all waves of few blocks
+  // (float16 4096x11008, 5.4 rounds: 51.0 us against 58.0).
   auto rb_of = [&](uint32_t t) { return bid + t * nblk; };
   auto advance = [&](uint32_t& t, uint32_t& j) {
-    const bool same = wave + (j + 1) * waves < CB;
+    const bool same = !DEC && wave + (j + 1) * waves < CB;
     t = same ? t : t + 1;
     j = same ? j + 1 : 0u;
   };
-  auto group = [&](uint32_t t, uint32_t j) { return min(rb_of(t) * CB + wave + j * waves, last_group); };
+  auto turn = [&](uint32_t t) {
+    const uint32_t base = t * nblk * waves;
+    return base + (base + nblk * waves <= RB * CB ? bid * waves + wave : wave * nblk + bid);
+  };
+  auto live = [&](uint32_t t) { return DEC ? turn(t) <= last_group : rb_of(t) < RB; };
+  auto group = [&](uint32_t t, uint32_t j) { return min(DEC ? turn(t) : rb_of(t) * CB + wave + j * waves, last_group); };
   auto lane_mu = [&](uint32_t rb) {
     const uint32_t G = min(16u, a.rows - rb * 16);
     return q * G + min(i, G - 1);
@@ -1953,7 +1965,7 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
   uint32_t t1 = 0, j1 = 0;
   advance(t1, j1);
   const uint32_t g0 = group(0, 0);
-  const uint32_t g1 = rb_of(t1) < RB ? group(t1, j1) : g0;
+  const uint32_t g1 = live(t1) ? group(t1, j1) : g0;
   uint32_t te[kBpPerThread];
   if constexpr (BP) bp_table_load(a.lut, te);
   else if constexpr (F16) table16_dma(a);
@@ -2015,22 +2027,23 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
   f32x4_t acce[NE];  // the other tiles' sums
 #pragma unroll
   for (int u = 0; u < NE; ++u) acce[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  for (uint32_t t = 0; rb_of(t) < RB; ++t) {
-    const uint32_t rb = rb_of(t);
+  uint32_t d_rb = m0.r0 / 16, d_c0 = m0.c0;  // decoding: the group's row block and first segment
+  for (uint32_t t = 0; live(t); ++t) {
+    const uint32_t rb = DEC ? d_rb : rb_of(t);
     const uint32_t G = min(16u, a.rows - rb * 16);
     const uint32_t mu = q * G + min(i, G - 1);
     const uint32_t sc_off = kTab + wave * kBuf + mu;
     const uint32_t* sc = s_dyn + sc_off;
-    for (uint32_t j = 0; j < nj; ++j) {
-      if (wave + j * waves >= CB) continue;
+    for (uint32_t j = 0; j < (DEC ? 1u : nj); ++j) {
+      if (!DEC && wave + j * waves >= CB) continue;
       // the next two groups of this wave
       uint32_t tn = t, jn = j;
       advance(tn, jn);
-      const bool okn = rb_of(tn) < RB;
+      const bool okn = live(tn);
       uint32_t t2 = tn, j2 = jn;
       advance(t2, j2);
-      const uint32_t g2 = rb_of(t2) < RB ? group(t2, j2) : group(t, j);
-      const uint32_t rbn = okn ? rb_of(tn) : rb;
+      const uint32_t g2 = live(t2) ? group(t2, j2) : group(t, j);
+      const uint32_t rbn = !okn ? rb : DEC ? m1.r0 / 16 : rb_of(tn);
       const uint32_t Gn = min(16u, a.rows - rbn * 16);
       const uint64_t n_first = m1.first;
       const uint32_t n_c0 = m1.c0;
@@ -2040,7 +2053,7 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
       m1 = load_meta(a, g2, lane);
       // prefetch source: the next group, else the lane's cached activations
       // (decoding: the current group's raw bytes)
-      const uint32_t cur_c0 = (wave + j * waves) * 4;
+      const uint32_t cur_c0 = DEC ? d_c0 : (wave + j * waves) * 4;
       const uint8_t* rbase = okn    ? a.raw + n_first * S
                              : DEC ? a.raw + ((uint64_t)rb * 16u * a.L + (uint64_t)cur_c0 * G) * S
                                    : xbytes + cur_c0 * XSEG;
@@ -2158,9 +2171,11 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
       wait_lgkm0();
       wave_sync_lds();
       pos2 = pos2n;
+      d_rb = rbn;
+      d_c0 = n_c0;
       // the next group's words go in now, unless this was the wave's last
       // group of the row block (the columns first carry the row block's sum)
-      if (okn && rb_of(tn) == rb) {
+      if (okn && (DEC || rb_of(tn) == rb)) {
         stream_store<JT>(cols, sw, lane);
         wait_lgkm0();
         wave_sync_lds();
@@ -2202,7 +2217,7 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
     }
     // the next group's words, held back for the sum (none after the last
     // row block, which has no next group)
-    if (rb_of(t + 1) < RB) {
+    if (!DEC && rb_of(t + 1) < RB) {
       stream_store<JT>(cols, sw, lane);
       wait_lgkm0();
       wave_sync_lds();
@@ -2720,14 +2735,35 @@ static uint32_t stream_waves(uint32_t most, size_t tab, size_t per_wave, uint32_
   return rounds > 1 && table < 2 ? std::min(w, ((CB + rounds - 1) / rounds + 3) & ~3u) : w;
 }
 
-static bool stream_shape(const hl_tensor* t, const GroupArgs& ga, int* jt, uint32_t* waves, size_t* per_wave) {
+// Stream words per lane the persistent kernel is built for (*jt), its LDS
+// bytes per wave and of the table; false when it is not built for the matrix
+// (16-row groups at S = 32 or 64, every segment within the largest word count).
+static bool stream_regions(const hl_tensor* t, const GroupArgs& ga, int* jt, size_t* per_wave, size_t* tab) {
   if (t->grp_rows != 16 || (t->seg_len != 64 && t->seg_len != 32)) return false;
-  const uint32_t CB = ga.CB, RB = ga.RB, cus = (uint32_t)device_cus();
   *jt = stream_rows_for(t->seg_len, ga.col_rows, is_fp16(t));
-  const size_t tab = is_fp16(t)         ? (size_t)ga.t16_words * 4
-                     : bounded_pairs(t) ? (size_t)kBpWords * 4
-                                        : (size_t)(kLutN + kAuxWords) * 4;
   *per_wave = (size_t)(*jt + 1) * kCol * 4;
+  *tab = is_fp16(t)         ? (size_t)ga.t16_words * 4
+         : bounded_pairs(t) ? (size_t)kBpWords * 4
+                            : (size_t)(kLutN + kAuxWords) * 4;
+  return *jt != 0;
+}
+
+// Its decode form takes matrices of at least kDecodeTurns groups for each of
+// its waves (8 a block, what the registers of a group's decoded weights
+// leave), whatever their shape: the groups go round.
+constexpr uint32_t kDecodeTurns = 2;
+static bool decode_shape(const hl_tensor* t, const GroupArgs& ga, int* jt, uint32_t* waves, size_t* per_wave) {
+  size_t tab = 0;
+  if (!stream_regions(t, ga, jt, per_wave, &tab)) return false;
+  *waves = stream_threads(true, stream_table(t)) / 64;
+  return tab + *waves * *per_wave <= kMaxLds &&
+         (uint64_t)ga.RB * ga.CB >= (uint64_t)kDecodeTurns * device_cus() * *waves;
+}
+
+static bool stream_shape(const hl_tensor* t, const GroupArgs& ga, int* jt, uint32_t* waves, size_t* per_wave) {
+  size_t tab = 0;
+  if (!stream_regions(t, ga, jt, per_wave, &tab)) return false;
+  const uint32_t CB = ga.CB, RB = ga.RB, cus = (uint32_t)device_cus();
   const int table = stream_table(t);
   const uint32_t w = stream_waves(stream_threads(false, table) / 64, tab, *per_wave, CB, (uint64_t)RB * CB, cus, table);
   *waves = w;
@@ -2736,7 +2772,7 @@ static bool stream_shape(const hl_tensor* t, const GroupArgs& ga, int* jt, uint3
   // 14336x4096 65.8 against 86.2 us). With them one is enough (4096x4096 20.2
   // against 20.3 us; decoding 4096x11008 55.8 against 98.8 us).
   const uint32_t min_rb = table == 2 ? 2 * cus : cus;
-  return *jt && w >= 8 && CB >= w && RB >= min_rb && (uint64_t)RB * CB >= 2ull * cus * w;
+  return w >= 8 && CB >= w && RB >= min_rb && (uint64_t)RB * CB >= 2ull * cus * w;
 }
 
 // The same for a product: float16 matrices of 8 column blocks and many row
@@ -2758,7 +2794,7 @@ extern "C" hl_status hl_decode(const hl_tensor* t, uint16_t* out_dev, void* stre
   int jt = 0;
   uint32_t w = 0;
   size_t per_wave = 0;
-  if (stream_shape(t, pl.ga, &jt, &w, &per_wave)) {
+  if (decode_shape(t, pl.ga, &jt, &w, &per_wave)) {
     GemvArgs p;
     std::memset(&p, 0, sizeof(p));
     p.g = pl.ga;
@@ -2766,9 +2802,7 @@ extern "C" hl_status hl_decode(const hl_tensor* t, uint16_t* out_dev, void* stre
     p.B = 1;
     p.C = pl.ga.CB;
     p.KS = 1;
-    // the kernel's bound when decoding (registers for a group's weights)
-    w = stream_threads(true, stream_table(t)) / 64;
-    const dim3 grid(std::min<uint32_t>(pl.ga.RB, (uint32_t)device_cus()));
+    const dim3 grid((uint32_t)device_cus());
     // float16: its tables lead the dynamic LDS
     if (is_fp16(t))
       return launch_stream16(false, true, flat_mh(t->cb16), t->seg_len, jt, grid, dim3(w * 64),
@@ -2776,8 +2810,7 @@ extern "C" hl_status hl_decode(const hl_tensor* t, uint16_t* out_dev, void* stre
     // the bounded-pair table where the encoder's joint limit holds (with the
     // whole-row stores it decodes 28672x8192 in 175.9 us against 187.7 us
     // with the joint table; stored straight from the lanes, 307 against 273)
-    return launch_stream_dec(t->seg_len, jt, bounded_pairs(t),
-                             dim3(std::min<uint32_t>(pl.ga.RB, (uint32_t)device_cus())), dim3(w * 64), w * per_wave,
+    return launch_stream_dec(t->seg_len, jt, bounded_pairs(t), grid, dim3(w * 64), w * per_wave,
                              (hipStream_t)stream, p);
   }
   if (is_fp16(t)) {
