@@ -1934,8 +1934,8 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
   // block to its row blocks: the waves of all blocks take the groups in turn
   // (round t, j = 0), so that no block is left with a row block more than the
   // others and no wave without a group at the end of each (5120x5120, 320 row
-  // blocks of 20 column blocks on 256 blocks of 8 waves: 31.5 us by row
-  // blocks, 26.2 us in turn). The last round's groups go to few waves of every
+  // blocks of 20 column blocks on 256 blocks of 8 waves: 31.6 us by row
+  // blocks, 23.3 us in turn). The last round's groups go to few waves of every
   // block, which then decode faster, instead of all waves of few blocks
   // (float16 4096x11008, 5.4 rounds: 51.0 us against 58.0).
   auto rb_of = [&](uint32_t t) { return bid + t * nblk; };
