@@ -303,8 +303,8 @@ hl_status hl_tensor_prepare(const hl_tensor* t, void* stream);
 hl_status hl_decode(const hl_tensor* t, uint16_t* out_dev, void* stream);
 
 /* Bytes of device workspace hl_decode_gemv may use for `t` at this batch
- * (the tiled activations of larger batches and the cross-block partial sums;
- * 0 on bad arguments). */
+ * (arrival counters, the tiled activations of larger batches and the
+ * cross-block partial sums; 0 when it uses none and on bad arguments). */
 size_t hl_gemv_workspace_bytes(const hl_tensor* t, uint32_t batch);
 
 /* y[b][r] = sum_k W[r][k] * x[b][k] for b < batch, decoding W on the fly in
@@ -313,7 +313,8 @@ size_t hl_gemv_workspace_bytes(const hl_tensor* t, uint32_t batch);
  * written). fp32 accumulation; every output is summed in a fixed order, so
  * results do not vary between runs. batch in [1, 16].
  * workspace_dev: hl_gemv_workspace_bytes(t, batch) bytes, zero-filled by the
- * caller once before first use; each call leaves it ready for the next. Calls
+ * caller once before first use; each call leaves it ready for the next, of
+ * any batch and on any matrix it is large enough for. Calls
  * that may run concurrently need separate workspaces. With NULL (or too
  * small) the product is still computed, with less parallelism for matrices
  * with few rows. Errors: HL_EINVAL (also for misaligned x, y or workspace). */
@@ -323,8 +324,8 @@ hl_status hl_decode_gemv(const hl_tensor* t, const void* x_dev, hl_dtype x_dtype
 
 /* hl_decode_gemv without a caller workspace, for callers that cannot
  * allocate device memory (code under HIP graph capture, serving loops that
- * forbid allocation): the tiled activations and partial sums go to a scratch
- * array of HL_NOALLOC_SCRATCH_BYTES that the library holds on each GPU it
+ * forbid allocation): the tiled activations, partial sums and arrival counters
+ * go to a scratch array (HL_NOALLOC_SCRATCH_BYTES and 4 KB) that the library holds on each GPU it
  * runs on until the process ends (its address is looked up on the first call
  * on a GPU). No device memory is allocated or freed. The arrival counters a
  * split product uses are zeroed by a small kernel on `stream` before it (no

@@ -2830,13 +2830,17 @@ extern "C" hl_status hl_decode(const hl_tensor* t, uint16_t* out_dev, void* stre
 
 static uint32_t ks_cap(uint32_t CB) { return std::min<uint32_t>(CB, 64); }
 
-// Workspace layout: the tiled copy of bf16 activations (batch above one,
-// 16-row groups: 32 bytes per column), then RB arrival counters and the
-// split partial sums of the non-persistent kernels.
+// Workspace layout: the arrival counters of split products, then the tiled
+// copy of 16-bit activations (batch above one, 16-row groups: 32 bytes per
+// column), then the partial sums of split products. The counters have this
+// place in every call, whatever its batch, matrix or kernel: nothing else is
+// written there and each call leaves them zero, so that calls of any batches
+// and matrices can follow each other on one workspace.
+constexpr uint32_t kSplitRowBlocks = 1024;  // most row blocks of a split product, one counter each
+constexpr uint64_t kCounterBytes = kSplitRowBlocks * 4;
 static uint64_t xtile_region(const hl_tensor* t, uint32_t batch) {
   return (batch > 1 && t->grp_rows == 16) ? ((uint64_t)t->cols * 32 + 255) & ~255ull : 0;
 }
-static uint64_t counter_bytes(uint32_t RB) { return ((uint64_t)RB * 4 + 255) & ~255ull; }
 
 // Column blocks per block (*C) and blocks per row block (*KS) of the
 // non-persistent kernels. A block of up to 8 waves decodes a group each in
@@ -2852,15 +2856,15 @@ static void split_shape(const Plan& pl, uint32_t* C_out, uint32_t* KS_out) {
   const uint32_t CB = pl.ga.CB, RB = pl.ga.RB;
   const uint32_t cus = (uint32_t)device_cus();
   uint32_t KS = 1;
-  if (CB > kWholeColumnBlocks)
+  if (CB > kWholeColumnBlocks && RB <= kSplitRowBlocks)
     KS = std::max<uint32_t>(1, std::min({cus / RB, (CB + kPartColumnBlocks - 1) / kPartColumnBlocks, ks_cap(CB)}));
   *C_out = (CB + KS - 1) / KS;
   *KS_out = (CB + *C_out - 1) / *C_out;
 }
 
-// Workspace bytes of a split over KS k-parts (counters and partial sums).
+// Bytes of the partial sums of a split over KS k-parts.
 static uint64_t split_bytes(const Plan& pl, uint32_t batch, uint32_t KS) {
-  return KS > 1 ? counter_bytes(pl.ga.RB) + (uint64_t)KS * batch * pl.ga.RB * pl.ga.GR * 4 : 0;
+  return KS > 1 ? (uint64_t)KS * batch * pl.ga.RB * pl.ga.GR * 4 : 0;
 }
 
 __global__ void __launch_bounds__(256) zero_kernel(uint32_t* p, uint32_t n) {
@@ -2870,15 +2874,14 @@ __global__ void __launch_bounds__(256) zero_kernel(uint32_t* p, uint32_t n) {
 // Split of the non-persistent kernels, with room for partials in the
 // workspace (else one block per row block). *block_waves = the waves a block
 // is launched with (no more than its column blocks). With `clear`, the
-// arrival counters are zeroed by a small kernel on `stream` first (a
-// workspace shared with calls of other shapes, whose bytes there are not
-// counters).
+// arrival counters are zeroed by a small kernel on `stream` first (memory
+// that an earlier call may not have left ready).
 static hl_status choose_split(const hl_tensor* t, const Plan& pl, uint32_t batch, void* workspace_dev,
                               size_t workspace_bytes, bool clear, hipStream_t stream, GemvArgs* p,
                               uint32_t* block_waves) {
   uint32_t C = 0, KS = 0;
   split_shape(pl, &C, &KS);
-  const uint64_t base = xtile_region(t, batch);
+  const uint64_t base = kCounterBytes + xtile_region(t, batch);
   if (KS > 1 && (!workspace_dev || workspace_bytes < base + split_bytes(pl, batch, KS))) {
     KS = 1;  // no room for partial sums: one block per row block
     C = pl.ga.CB;
@@ -2887,9 +2890,8 @@ static hl_status choose_split(const hl_tensor* t, const Plan& pl, uint32_t batch
   p->KS = KS;
   *block_waves = std::min<uint32_t>(pl.waves, C);
   if (KS > 1) {
-    uint8_t* w = reinterpret_cast<uint8_t*>(workspace_dev) + base;
-    p->counter = reinterpret_cast<uint32_t*>(w);
-    p->partial = reinterpret_cast<float*>(w + counter_bytes(pl.ga.RB));
+    p->counter = reinterpret_cast<uint32_t*>(workspace_dev);
+    p->partial = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(workspace_dev) + base);
     if (clear) return launch(zero_kernel, dim3((pl.ga.RB + 255) / 256), dim3(256), 0, stream, p->counter, pl.ga.RB);
   }
   return HL_OK;
@@ -2929,8 +2931,8 @@ static hl_status tile_activations(const hl_tensor* t, const void* x_dev, uint32_
   *xt = false;
   const uint64_t n = t->rows * t->cols;
   const bool want = batch >= 12 || (batch >= 5 && n >= (32ull << 20)) || (batch >= 4 && n >= (128ull << 20));
-  if (!want || !workspace_dev || workspace_bytes < xtile_region(t, batch)) return HL_OK;
-  uint4* tile = reinterpret_cast<uint4*>(workspace_dev);
+  if (!want || !workspace_dev || workspace_bytes < kCounterBytes + xtile_region(t, batch)) return HL_OK;
+  uint4* tile = reinterpret_cast<uint4*>(reinterpret_cast<uint8_t*>(workspace_dev) + kCounterBytes);
   const uint32_t chunks = (uint32_t)(t->cols / 8);
   const hl_status st = launch(xtile_kernel<16>, dim3((chunks * 16 + 255) / 256), dim3(256), 0, stream,
                               reinterpret_cast<const uint4*>(x_dev), batch, chunks, tile);
@@ -2997,33 +2999,42 @@ static hl_status gemv_plan(const hl_tensor* t, hl_dtype x_dtype, uint32_t batch,
   return HL_OK;
 }
 
-// Workspace bytes a product uses at most (tiled activations, counters and
-// partial sums); 0 for bad arguments.
-static uint64_t gemv_need(const hl_tensor* t, hl_dtype x_dtype, uint32_t batch) {
+// Workspace a product uses at most: tiled activations, partial sums and (of
+// kCounterBytes) arrival counters; all 0 for bad arguments.
+struct GemvNeed {
+  uint64_t tile = 0, parts = 0, counters = 0;
+  uint64_t bytes() const { return tile + parts ? kCounterBytes + tile + parts : 0; }
+};
+static GemvNeed gemv_need(const hl_tensor* t, hl_dtype x_dtype, uint32_t batch) {
   Plan pl;
+  GemvNeed need;
+  bool persistent = false;
   if (is_fp16(t)) {
-    if (x_dtype != HL_F16 || make_plan(t, 0, false, &pl) != HL_OK) return 0;
+    if (x_dtype != HL_F16 || make_plan(t, 0, false, &pl) != HL_OK) return need;
     int jt = 0;
     uint32_t w = 0;
     size_t per_wave = 0;
-    if (stream_product(t, pl.ga, &jt, &w, &per_wave)) return xtile_region(t, batch);
+    persistent = stream_product(t, pl.ga, &jt, &w, &per_wave);
   } else {
-    bool mfma = false, persistent = false;
+    bool mfma = false;
     uint32_t xw = 0;
-    if (x_dtype == HL_F16 || gemv_plan(t, x_dtype, batch, &pl, &mfma, &persistent, &xw) != HL_OK) return 0;
-    if (persistent) return xtile_region(t, batch);
+    if (x_dtype == HL_F16 || gemv_plan(t, x_dtype, batch, &pl, &mfma, &persistent, &xw) != HL_OK) return need;
   }
+  need.tile = xtile_region(t, batch);
+  if (persistent) return need;
   uint32_t C = 0, KS = 0;
   split_shape(pl, &C, &KS);
-  return xtile_region(t, batch) + split_bytes(pl, batch, KS);
+  need.parts = split_bytes(pl, batch, KS);
+  need.counters = KS > 1 ? ((uint64_t)pl.ga.RB * 4 + 255) & ~255ull : 0;
+  return need;
 }
 
 extern "C" size_t hl_gemv_workspace_bytes(const hl_tensor* t, uint32_t batch) {
   if (!t || t->seg_len == 0 || t->grp_rows == 0 || t->grp_rows > HL_GROUP_SEGS || batch < 1 ||
       batch > HL_MAX_BATCH)
     return 0;
-  if (is_fp16(t)) return (size_t)gemv_need(t, HL_F16, batch);
-  return (size_t)std::max(gemv_need(t, HL_F32, batch), gemv_need(t, HL_BF16, batch));
+  if (is_fp16(t)) return (size_t)gemv_need(t, HL_F16, batch).bytes();
+  return (size_t)std::max(gemv_need(t, HL_F32, batch).bytes(), gemv_need(t, HL_BF16, batch).bytes());
 }
 
 static hl_status gemv_args_ok(const hl_tensor* t, const void* x_dev, hl_dtype x_dtype, uint32_t batch,
@@ -3110,7 +3121,10 @@ extern "C" hl_status hl_decode_gemv(const hl_tensor* t, const void* x_dev, hl_dt
 // runs on, held until the process ends. In host code `scratch` is a
 // stand-in, not a device address: the address of a GPU's copy comes from
 // hipGetSymbolAddress (with that GPU current) and is what the kernels get.
-static __device__ __align__(256) uint8_t scratch[HL_NOALLOC_SCRATCH_BYTES];
+// The limit of what a product may need counts the counters it uses, not the
+// whole place kept for them.
+constexpr uint64_t kScratchBytes = kCounterBytes + HL_NOALLOC_SCRATCH_BYTES;
+static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 
 static std::mutex g_scratch_mu;
 static void* g_scratch[kMaxDevices];
@@ -3134,12 +3148,12 @@ extern "C" hl_status hl_decode_gemv_noalloc(const hl_tensor* t, const void* x_de
                                             float* y_dev, void* stream) {
   hl_status st = gemv_args_ok(t, x_dev, x_dtype, batch, y_dev);
   if (st != HL_OK) return st;
-  const uint64_t need = gemv_need(t, x_dtype, batch);
-  if (need > HL_NOALLOC_SCRATCH_BYTES) return HL_EUNSUPPORTED;
+  const GemvNeed need = gemv_need(t, x_dtype, batch);
+  if (need.tile + need.parts + need.counters > HL_NOALLOC_SCRATCH_BYTES) return HL_EUNSUPPORTED;
   void* ws = nullptr;
   st = scratch_address(&ws);
   if (st != HL_OK) return st;
-  return gemv_impl(t, x_dev, x_dtype, batch, y_dev, ws, HL_NOALLOC_SCRATCH_BYTES, true, (hipStream_t)stream);
+  return gemv_impl(t, x_dev, x_dtype, batch, y_dev, ws, kScratchBytes, true, (hipStream_t)stream);
 }
 
 // Shape of a grouped launch of the persistent kernel over ts[0..count) (bf16
@@ -3206,9 +3220,9 @@ static hl_status gemv_multi_impl(const hl_tensor* const* ts, uint32_t count, con
   // matrices one after another.
   GroupShape g;
   if (!(x_dtype == HL_BF16 && group_shape(ts, count, &g))) {
-    // one product after another on the shared workspace: a split product
-    // zeroes its counters first (another matrix's product may have left
-    // partial sums where they lie)
+    // one product after another on the shared workspace; a split product
+    // zeroes its counters first (a group that one launch takes needs no
+    // zeroed workspace, so a caller may not have one)
     for (uint32_t k = 0; k < count; ++k) {
       hl_status st = gemv_args_ok(ts[k], x_dev, x_dtype, batch, y_devs[k]);
       if (st == HL_OK)
