@@ -346,7 +346,8 @@ class DeviceTensor:
         if ws is None or ws.numel() < need:
             ws = torch.zeros(max(need, 4), dtype=torch.uint8, device=self.blob.device)
             self._ws = ws
-        self._ws_batch = batch  # need grows with the batch
+        if 1 <= batch <= MAX_BATCH:  # other batches have no size (0); between these it grows with the batch
+            self._ws_batch = batch
         return ws
 
     def gemv(self, x, y=None, stream=None, workspace=None):
