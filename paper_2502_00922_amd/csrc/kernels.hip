@@ -2339,6 +2339,7 @@ static uint32_t longest_exponent_code(const hl_tensor* t) {
 struct Plan {
   GroupArgs ga;
   bool one;           // the single bounded-pair table (matrix-core kernels of small matrices)
+  bool vector;        // raw plane and activations in the wave regions (vector kernel, general decode)
   uint32_t waves;
   size_t lds;       // dynamic LDS: (float16 tables) + the wave regions
   size_t tab_dyn;   // bytes of the float16 tables in it
@@ -2391,6 +2392,7 @@ static hl_status make_plan(const hl_tensor* t, uint32_t extra_words_per_wave, bo
     a.t16_aux = lay.aux;
     a.t16_words = lay.words;
   }
+  pl->vector = raw_lds;
   pl->one = !raw_lds && longest_exponent_code(t) <= (uint32_t)kBpBits;
   const size_t tab_static = is_fp16(t) ? 0 : (size_t)(pl->one ? kBpN : kLutN + kAuxWords) * 4;
   pl->tab_static = tab_static;
@@ -2842,29 +2844,64 @@ static uint64_t xtile_region(const hl_tensor* t, uint32_t batch) {
   return (batch > 1 && t->grp_rows == 16) ? ((uint64_t)t->cols * 32 + 255) & ~255ull : 0;
 }
 
+// Bytes of the partial sums of a split over KS k-parts.
+static uint64_t split_bytes(const Plan& pl, uint32_t batch, uint32_t KS) {
+  return KS > 1 ? (uint64_t)KS * batch * pl.ga.RB * pl.ga.GR * 4 : 0;
+}
+// Bytes of the counters that a split product uses.
+static uint64_t used_counter_bytes(uint32_t RB) { return ((uint64_t)RB * 4 + 255) & ~255ull; }
+
+// Time of the vector kernel's product in KS parts, in the time that a wave
+// takes for a group: the turns of a CU's blocks (one fits with the regions
+// that leave few waves), each the rounds of its waves and a fixed part (table,
+// first loads, sum of the waves; about one group of 64-weight segments, twice
+// that at batch 16), and the meeting of the parts.
+static double vector_time(const Plan& pl, uint32_t batch, uint32_t cus, uint32_t KS) {
+  const uint32_t C = (pl.ga.CB + KS - 1) / KS, w = std::min(pl.waves, C);
+  const double unit = 64.0 / pl.ga.S;
+  return ((uint64_t)pl.ga.RB * KS + cus - 1) / cus * (unit * (1 + batch / 16.0) + (C + w - 1) / w) +
+         (KS > 1 ? 0.5 * unit : 0.0);
+}
+
 // Column blocks per block (*C) and blocks per row block (*KS) of the
 // non-persistent kernels. A block of up to 8 waves decodes a group each in
 // little more than the time of one, and meeting the other parts through
 // memory costs 2.5 to 3 us: a row block of at most 8 column blocks is one
 // block (1024x1024, 4 column blocks: 7.8 us as one block, 16.7 us in four
-// parts at the time, 10.0 in two). Longer ones are split into parts of 4 or
-// more, as many as keep every part on a CU of its own (1000x4096: 11.3 us in
+// parts at the time, 10.0 in two). Longer ones are split into parts of about
+// 4, as many as keep every part on a CU of its own (1000x4096: 11.3 us in
 // 4 parts, 12.3 whole; 256x8192: 11.5 in 8, 18.9 whole; more parts than CUs
-// lose: 3500x4096 12.8 us whole, 16.0 in two).
+// lose: 3500x4096 12.4 us whole, 14.6 in two and 14.1 in four; 2560x10240 21.9
+// whole, 34.9 in two and 24.1 in five; 2064x28672 44.9, 55.1 and 52.1).
+//
+// The vector kernel's regions (raw plane and activations) leave fewer waves
+// the longer the segments and the larger the batch; a part's waves then take
+// rounds of long groups, and more parts pay although they take turns on a CU:
+// as many as the estimate above says are shortest (float32 x, 512-weight
+// segments: 500x3072 at batch 1 37.8 us in 3 parts, 100 whole, at batch 16 83
+// in 6, 414 whole; 8317x10240, 130 row blocks of 64 rows, 207 and 324; the
+// estimate's choice is within 0.5% of the best over 272 shapes of 1 to 7
+// waves). They also stay within the memory of the
+// allocation-free product, which then takes what it takes without them.
 constexpr uint32_t kWholeColumnBlocks = 8, kPartColumnBlocks = 4;
-static void split_shape(const Plan& pl, uint32_t* C_out, uint32_t* KS_out) {
+static void split_shape(const hl_tensor* t, const Plan& pl, uint32_t batch, uint32_t* C_out, uint32_t* KS_out) {
   const uint32_t CB = pl.ga.CB, RB = pl.ga.RB;
   const uint32_t cus = (uint32_t)device_cus();
   uint32_t KS = 1;
   if (CB > kWholeColumnBlocks && RB <= kSplitRowBlocks)
     KS = std::max<uint32_t>(1, std::min({cus / RB, (CB + kPartColumnBlocks - 1) / kPartColumnBlocks, ks_cap(CB)}));
+  if (pl.vector && RB <= kSplitRowBlocks) {
+    double best = vector_time(pl, batch, cus, KS);
+    for (uint32_t k = KS + 1; k <= ks_cap(CB); ++k) {
+      const double time = vector_time(pl, batch, cus, k);
+      if (time >= 0.95 * best) continue;
+      if (xtile_region(t, batch) + split_bytes(pl, batch, k) + used_counter_bytes(RB) > HL_NOALLOC_SCRATCH_BYTES) break;
+      best = time;
+      KS = k;
+    }
+  }
   *C_out = (CB + KS - 1) / KS;
   *KS_out = (CB + *C_out - 1) / *C_out;
-}
-
-// Bytes of the partial sums of a split over KS k-parts.
-static uint64_t split_bytes(const Plan& pl, uint32_t batch, uint32_t KS) {
-  return KS > 1 ? (uint64_t)KS * batch * pl.ga.RB * pl.ga.GR * 4 : 0;
 }
 
 __global__ void __launch_bounds__(256) zero_kernel(uint32_t* p, uint32_t n) {
@@ -2880,7 +2917,7 @@ static hl_status choose_split(const hl_tensor* t, const Plan& pl, uint32_t batch
                               size_t workspace_bytes, bool clear, hipStream_t stream, GemvArgs* p,
                               uint32_t* block_waves) {
   uint32_t C = 0, KS = 0;
-  split_shape(pl, &C, &KS);
+  split_shape(t, pl, batch, &C, &KS);
   const uint64_t base = kCounterBytes + xtile_region(t, batch);
   if (KS > 1 && (!workspace_dev || workspace_bytes < base + split_bytes(pl, batch, KS))) {
     KS = 1;  // no room for partial sums: one block per row block
@@ -3023,9 +3060,9 @@ static GemvNeed gemv_need(const hl_tensor* t, hl_dtype x_dtype, uint32_t batch) 
   need.tile = xtile_region(t, batch);
   if (persistent) return need;
   uint32_t C = 0, KS = 0;
-  split_shape(pl, &C, &KS);
+  split_shape(t, pl, batch, &C, &KS);
   need.parts = split_bytes(pl, batch, KS);
-  need.counters = KS > 1 ? ((uint64_t)pl.ga.RB * 4 + 255) & ~255ull : 0;
+  need.counters = KS > 1 ? used_counter_bytes(pl.ga.RB) : 0;
   return need;
 }
 
@@ -3033,8 +3070,11 @@ extern "C" size_t hl_gemv_workspace_bytes(const hl_tensor* t, uint32_t batch) {
   if (!t || t->seg_len == 0 || t->grp_rows == 0 || t->grp_rows > HL_GROUP_SEGS || batch < 1 ||
       batch > HL_MAX_BATCH)
     return 0;
-  if (is_fp16(t)) return (size_t)gemv_need(t, HL_F16, batch).bytes();
-  return (size_t)std::max(gemv_need(t, HL_F32, batch).bytes(), gemv_need(t, HL_BF16, batch).bytes());
+  // enough for smaller batches too, which may take more parts
+  uint64_t bytes = 0;
+  for (uint32_t b = 1; b <= batch; ++b)
+    for (hl_dtype x : {HL_F32, HL_BF16, HL_F16}) bytes = std::max(bytes, gemv_need(t, x, b).bytes());
+  return (size_t)bytes;
 }
 
 static hl_status gemv_args_ok(const hl_tensor* t, const void* x_dev, hl_dtype x_dtype, uint32_t batch,
