@@ -393,7 +393,11 @@ __device__ __attribute__((always_inline)) inline uint32_t long_pair(uint32_t ent
   return (ua + ub) | ((uint32_t)((a << 4) | b) << 23);
 }
 
-// The four table reads of the window W0 again, resolving long pairs.
+// The four table reads of the window W0 again, resolving long pairs. After
+// long pairs the rest of the window can end within a pair, which the table
+// then reads as followed by zeros: the pair that it finds there also reaches
+// past the window's 62 bits (a code that the bits left hold whole would be the
+// true one), and is left as an escape.
 __device__ __attribute__((always_inline)) inline void redo4(uint64_t W0, uint32_t* e) {
   uint64_t W = W0;
   uint32_t used = 0;
@@ -401,6 +405,7 @@ __device__ __attribute__((always_inline)) inline void redo4(uint64_t W0, uint32_
   for (int k = 0; k < 4; ++k) {
     uint32_t ent = lut_at((uint32_t)W);
     if ((int)ent < 0) ent = long_pair(ent, W, used);
+    else if (used + (ent & 0x3F) > 62) ent = kEsc;
     W = shift_window(W, ent);
     used += ent & 0x3F;
     e[k] = ent;
