@@ -3329,14 +3329,15 @@ extern "C" size_t hl_gemm_workspace_bytes(const hl_tensor* t, uint32_t tokens) {
 }
 
 // One hipBLASLt handle per GPU, created on first use with that GPU current,
-// and the algorithms last chosen there (see LtGemm::find), by size.
+// and the algorithms last chosen there (see LtGemm::find), by size: a model's
+// handful of shapes at a hundred prompt lengths.
 struct LtChoice {
   uint64_t rows, cols;
   uint32_t tokens;  // 0: no entry
   bool found;
   hipblasLtMatmulAlgo_t algo;
 };
-constexpr int kLtChoices = 64;
+constexpr int kLtChoices = 512;
 static std::mutex g_lt_mu;
 static hipblasLtHandle_t g_lt[kMaxDevices];
 static LtChoice g_lt_choice[kMaxDevices][kLtChoices];
@@ -3378,8 +3379,11 @@ struct LtGemm {
   // algorithm that divides the sums over blocks then says how much its
   // partial tiles take, while asked with no room it answers with the same
   // algorithm and a need of zero, and stores them past a null pointer
-  // (2605x22784 at 200 tokens: 28.9 MB). Looking through its answers takes
-  // up to milliseconds of host time, so the choice is kept for its size.
+  // (2605x22784 at 200 tokens: 28.9 MB). Its 16 answers for a new size take 60
+  // to 135 us of host time (a first question for one answer only would make
+  // the longer list of the same size take 24 to 48 ms), asked again 3 to 65,
+  // so the choice is kept for its size. A question that failed counts for
+  // its call alone, and none holds up other threads' calls.
   hl_status find(uint64_t rows, uint64_t cols, uint32_t tokens) {
     int dev = 0;
     hl_status st = lt_handle(&h, &dev);
@@ -3392,12 +3396,14 @@ struct LtGemm {
         hipblasLtMatrixLayoutCreate(&lb, HIP_R_16BF, cols, tokens, (int64_t)cols) != HIPBLAS_STATUS_SUCCESS ||
         hipblasLtMatrixLayoutCreate(&ld, HIP_R_32F, rows, tokens, (int64_t)rows) != HIPBLAS_STATUS_SUCCESS)
       return HL_EHIP;
-    std::lock_guard<std::mutex> lock(g_lt_mu);
-    for (const LtChoice& c : g_lt_choice[dev])
-      if (c.tokens == tokens && c.rows == rows && c.cols == cols) {
-        algo = c.algo;
-        return c.found ? HL_OK : HL_EUNSUPPORTED;
-      }
+    {
+      std::lock_guard<std::mutex> lock(g_lt_mu);
+      for (const LtChoice& c : g_lt_choice[dev])
+        if (c.tokens == tokens && c.rows == rows && c.cols == cols) {
+          algo = c.algo;
+          return c.found ? HL_OK : HL_EUNSUPPORTED;
+        }
+    }
     const uint64_t room = 1ull << 40;
     constexpr int kAsk = 16;
     hipblasLtMatmulHeuristicResult_t heur[kAsk];
@@ -3409,11 +3415,13 @@ struct LtGemm {
             HIPBLAS_STATUS_SUCCESS &&
         hipblasLtMatmulAlgoGetHeuristic(h, op, la, lb, ld, ld, pref, kAsk, heur, &found) == HIPBLAS_STATUS_SUCCESS;
     if (pref) hipblasLtMatmulPreferenceDestroy(pref);
+    if (!asked) return HL_EUNSUPPORTED;
     LtChoice c = {rows, cols, tokens, false, {}};
-    for (int k = 0; asked && k < std::min(found, kAsk) && !c.found; ++k)
-      if (heur[k].workspaceSize == 0) c.algo = heur[k].algo, c.found = true;
-    g_lt_choice[dev][g_lt_next[dev]++ % kLtChoices] = c;
+    for (int k = 0; k < std::min(found, kAsk) && !c.found; ++k)
+      if (heur[k].state == HIPBLAS_STATUS_SUCCESS && heur[k].workspaceSize == 0) c.algo = heur[k].algo, c.found = true;
     algo = c.algo;
+    std::lock_guard<std::mutex> lock(g_lt_mu);
+    g_lt_choice[dev][g_lt_next[dev]++ % kLtChoices] = c;
     return c.found ? HL_OK : HL_EUNSUPPORTED;
   }
 
