@@ -371,9 +371,12 @@ size_t hl_gemm_workspace_bytes(const hl_tensor* t, uint32_t tokens);
  * columns of 16 words or more); otherwise, up to 64 tokens, each 16-row x 4-segment
  * weight tile is decoded once per chunk of up to 128 tokens and multiplied
  * with all of them on the matrix cores (Sec. 3.2: weights decompressed only
- * to be multiplied); every output summed in a fixed order; beyond that, where the product is compute-bound (Sec. 5), the
- * matrix is decoded once into the workspace (hl_decode) and multiplied by
- * hipBLASLt. x_dev: [tokens][cols] bf16; y_dev: [tokens][rows] float32 (fully
+ * to be multiplied). Beyond that, where the product is compute-bound (Sec. 5),
+ * the matrix is decoded once into the workspace (hl_decode) and multiplied by
+ * hipBLASLt; where that has no algorithm without a workspace of its own (few
+ * output tiles and long sums), by the fused kernel, or, with segments too long
+ * for it, by hl_gemv_bf16 in batches of 16 tokens. Every output of the fused
+ * kernels is summed in a fixed order. x_dev: [tokens][cols] bf16; y_dev: [tokens][rows] float32 (fully
  * written); fp32 accumulation. bf16 formats (split or whole exponent) with
  * 16-row groups and S = 32 or 64; others give HL_EUNSUPPORTED.
  * workspace_dev: hl_gemm_workspace_bytes(t, tokens) bytes (no initial

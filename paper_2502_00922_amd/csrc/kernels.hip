@@ -3527,7 +3527,19 @@ extern "C" hl_status hl_decode_gemm(const hl_tensor* t, const void* x_dev, hl_dt
   while (nt < kGemmMaxTiles && nt * 16 < tokens) nt *= 2;
   while (nt > 1 && tab + (size_t)nt * SP * 1024 + cols_bytes > kMaxLds) nt /= 2;
   const size_t slice = (size_t)nt * SP * 1024;
-  if (tab + slice + cols_bytes > kMaxLds) return HL_EUNSUPPORTED;
+  if (tab + slice + cols_bytes > kMaxLds) {
+    // a segment too long for the fused kernel's columns (codes of 12 bits a
+    // weight and more): beyond 64 tokens the workspace holds the decoded
+    // weights, multiplied by the vector kernel, 16 tokens at a time
+    if (tokens <= kGemmFusedMaxTokens) return HL_EUNSUPPORTED;
+    uint16_t* w = reinterpret_cast<uint16_t*>(workspace_dev);
+    st = hl_decode(t, w, stream);
+    const uint16_t* xs = reinterpret_cast<const uint16_t*>(x_dev);
+    for (uint32_t n = 0; n < tokens && st == HL_OK; n += HL_MAX_BATCH)
+      st = hl_gemv_bf16(w, t->rows, t->cols, xs + (uint64_t)n * t->cols, HL_BF16,
+                        std::min<uint32_t>(HL_MAX_BATCH, tokens - n), y_dev + (uint64_t)n * t->rows, stream);
+    return st;
+  }
   GemmArgs p;
   std::memset(&p, 0, sizeof(p));
   p.g = pl.ga;
