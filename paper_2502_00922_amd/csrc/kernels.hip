@@ -1873,16 +1873,23 @@ __device__ inline const GemvArgs& gemv_args(const Args& x) {
 // NT = 16-token tiles of activations per matrix instruction step: 1 (up to 16
 // activation rows), or 2 or 4 for prefill products of 17 to 32 or 33 to 64
 // tokens (one bf16 matrix, activations from their tiled copy).
-// Blocks of at most 16 waves (8 decoding, whose registers hold a group's
-// weights until its stores, or with several tiles; 12 for the float16
-// product, whose longer stream columns need more registers).
+// Blocks of at most 16 waves; 8 decoding (the registers hold a group's weights
+// until its stores), 12 with four tiles or float16's three tables.
 constexpr uint32_t stream_threads(bool dec, int tb, int nt = 1) {
   return dec ? 512 : nt == 4 ? 768 : tb == 2 ? 768 : 1024;
 }
 // Steps that activations are loaded ahead of their product: a whole group
-// (its registers: 4 SP NT), or with several tiles as many as leave registers
-// for these blocks.
-constexpr int stream_ahead(int sp, int nt) { return nt == 4 ? 2 : nt == 2 ? 4 : sp; }
+// (its registers: 4 SP NT), or as many as leave registers for these blocks
+// without spills: fewer with several tiles, and again fewer where the rest
+// takes more of them, with flat float16 codes (a whole group ahead spilled 19
+// to 26 registers: 14336x4096 56.9 us, 55.6 with four steps) and with the
+// joint table's longest columns (6 and, with two tiles, 11 spilled: 11008x4096
+// whole exponent, 449-bit segments, 28.3 -> 27.2 us at one row, 39.5 -> 36.8 at
+// 24).
+constexpr int stream_ahead(int sp, int jt, int nt, int tb) {
+  const bool tight = tb == 3 || (tb == 0 && jt == 20);
+  return nt == 4 ? 2 : nt == 2 ? (tight ? 2 : 4) : sp == 8 && tight ? 4 : sp;
+}
 
 template <int SP, int JT, bool XT, class Args, bool DEC, int TB, int NT = 1>
 __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kernel(Args sa) {
@@ -1982,7 +1989,7 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
   uint32_t pos2 = stream_load<JT>(a, m0, lane, sw) - kOld;
   uint2 rw[F16 ? 1 : SP];  // raw bytes of the next group's steps (bf16 formats)
   Signs<SP> sg, sgn;       // float16: the lane's sign bytes of this and the next group
-  constexpr int XD = stream_ahead(SP, NT);
+  constexpr int XD = stream_ahead(SP, JT, NT, TB);
   static_assert(SP % XD == 0, "the next group's activations fall in the same registers");
   uint4 xv[XD];
   uint4 xe[NE][XD];  // the other tiles' activations
