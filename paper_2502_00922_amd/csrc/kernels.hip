@@ -2789,12 +2789,14 @@ static bool stream_shape(const hl_tensor* t, const GroupArgs& ga, int* jt, uint3
   return w >= 8 && CB >= w && RB >= min_rb && (uint64_t)RB * CB >= 2ull * cus * w;
 }
 
-// The same for a product: float16 matrices of 8 column blocks and many row
-// blocks stay on the non-persistent kernel, two 8-wave blocks on a CU
-// (28672x2048 53.3 us there, 61.9 us here; 28000x2304, 9 column blocks,
-// 95.0 and 68.9).
+// The same for a product: float16 matrices of 8 column blocks stay on the
+// non-persistent kernel where two of its blocks (8 waves, a group each) fit a
+// CU: 8192x2048 20.9 us there, 22.2 here, 14336x2048 35.5 and 39.0,
+// 28672x2048 58.6 and 64.9; where the columns of longer segments leave room
+// for one, 20000x2048 takes 66.4 there and 48.7 here. (28000x2304, 9 column
+// blocks, 95.0 and 68.9.)
 static bool stream_product(const hl_tensor* t, const GroupArgs& ga, int* jt, uint32_t* waves, size_t* per_wave) {
-  if (is_fp16(t) && ga.CB == 8 && (uint64_t)ga.RB * ga.CB >= 18ull * device_cus()) return false;
+  if (is_fp16(t) && ga.CB == 8 && 2 * ((size_t)ga.t16_words + 8 * ga.col_rows * kCol) * 4 <= kMaxLds) return false;
   return stream_shape(t, ga, jt, waves, per_wave);
 }
 
