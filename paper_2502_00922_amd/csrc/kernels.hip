@@ -841,9 +841,11 @@ __device__ inline void part_store(float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Counts the wave's block in (its partial sums, stored by this wave, first);
-// true for the last of the KS blocks, whose later loads see every part. The
-// counter is back at zero then.
+// Counts the wave's block in; true for the last of the KS blocks, whose later
+// loads see every part. The counter is back at zero then. One wave of each
+// block calls it, and has itself stored all of the block's parts by
+// part_store: its own stores are all that it waits for, and only atomics of
+// agent scope pass the caches (part_sum loads them so).
 __device__ inline bool last_to_arrive(uint32_t* counter, uint32_t KS, uint32_t lane) {
   wait_vm0();
   uint32_t old = 0;
@@ -1742,7 +1744,8 @@ struct Signs {
 // instruction (16-row groups, float16 x): the bf16 matrix-core kernel's
 // structure (lane 16q + i decodes row i of segment q; the A operand is its 8
 // weights, the B operand x[n = i][8 activations]), with the float16 decode
-// (two table reads per weight) and one sign load per lane and group.
+// (three table reads per weight, or one with flat mh codes) and one sign load
+// per lane and group.
 template <int SP, bool XT, bool FLAT>
 __global__ void __launch_bounds__(1024) gemv16_mfma_kernel(GemvArgs p) {
   constexpr int KP = SP < 8 ? SP : SP == 8 ? 8 : 4;
@@ -1828,13 +1831,15 @@ __global__ void __launch_bounds__(1024) gemv16_mfma_kernel(GemvArgs p) {
 
 // ------------------------------------------------------------------ persistent fused GEMV
 
-// Persistent form of the matrix-core kernel for S = 8*SP (SP = 4 or 8) and matrices with at
-// least one 16-row block per block of the grid and at least as many column
-// blocks as waves. Block b takes row blocks b, b + grid, ...; its waves take
-// the row block's column blocks wave, wave + waves, ... The table is copied
-// once per block. With DEC it decodes to bf16 instead (hl_decode): a lane
-// keeps its segment's weights (S*2 bytes of one row) and stores them at the
-// group's end, with no activations and no sums.
+// Persistent form of the matrix-core kernel for S = 8*SP (SP = 4 or 8) and
+// matrices with at least one 16-row block per block of the grid and at least
+// as many column blocks as waves. Block b takes row blocks b, b + grid, ...;
+// its waves take the row block's column blocks wave, wave + waves, ... The
+// table is copied once per block. With DEC it decodes to 16-bit weights
+// instead (hl_decode), of matrices of any shape whose groups give every wave
+// two or more: the waves of all blocks take the groups in turn, a lane keeps
+// its segment's weights (S*2 bytes of one row) and stores them at the group's
+// end, with no activations and no sums.
 //
 // While a wave decodes group k from its LDS columns, group k+1's stream words
 // (JT per lane, four per load), raw bytes and activations are loaded into
@@ -1946,8 +1951,8 @@ __global__ void __launch_bounds__(stream_threads(DEC, TB, NT)) gemv_stream_kerne
   // block to its row blocks: the waves of all blocks take the groups in turn
   // (round t, j = 0), so that no block is left with a row block more than the
   // others and no wave without a group at the end of each (5120x5120, 320 row
-  // blocks of 20 column blocks on 256 blocks of 8 waves: 31.6 us by row
-  // blocks, 23.3 us in turn). The last round's groups go to few waves of every
+  // blocks of 20 column blocks on 256 blocks of 8 waves, container in the
+  // caches: 31.6 us by row blocks, 23.3 us in turn). The last round's groups go to few waves of every
   // block, which then decode faster, instead of all waves of few blocks
   // (float16 4096x11008, 5.4 rounds: 51.0 us against 58.0).
   auto rb_of = [&](uint32_t t) { return bid + t * nblk; };
@@ -2714,11 +2719,6 @@ extern "C" hl_status hl_tensor_prepare(const hl_tensor* t, void* stream) {
 }
 
 
-// Launch shape of the persistent kernel for one matrix: stream words per lane
-// (*jt), waves per block (*waves) and LDS bytes per wave; false when the
-// matrix does not fit it (16-row groups of the bf16 formats at S = 32 or 64,
-// at least one row block per CU and two groups per wave of at least 8 waves
-// per block, every segment within the largest stream word count).
 // The persistent kernel's bounded-pair form applies (S = 64, pairs within
 // the 11-bit window).
 static bool bounded_pairs(const hl_tensor* t) {
@@ -2732,9 +2732,8 @@ static int stream_table(const hl_tensor* t) {
 
 // Waves per block of the persistent kernel: at most `most`, what the LDS
 // holds, and the column blocks (a 14336x2560 product of 10 waves takes 21.1
-// us, 29.5 on the non-persistent kernel; 20000x3840 31.8 and 51.2; decoding
-// them 38.8 and 62.1, 59.0 and 120.8); fewer when that gives every wave two
-// groups (the second group's loads then overlap the first one's decode). The
+// us, 29.5 on the non-persistent kernel; 20000x3840 31.8 and 51.2); fewer
+// when that gives every wave two groups (the second group's loads then overlap the first one's decode). The
 // bf16 formats take no more than a row block's rounds need, in fours (one for
 // each SIMD): q, k and v of 4096 and twice 1024 rows by 4096 are 16 column
 // blocks, two rounds of 8 waves as of 12 (19.2 us, 20.7 with 12). Float16's
@@ -2774,6 +2773,10 @@ static bool decode_shape(const hl_tensor* t, const GroupArgs& ga, int* jt, uint3
          (uint64_t)ga.RB * ga.CB >= (uint64_t)kDecodeTurns * device_cus() * *waves;
 }
 
+// Launch shape of its products of one matrix: stream words per lane (*jt),
+// waves per block (*waves) and LDS bytes per wave; false when the matrix does
+// not fit it (what stream_regions asks, at least one row block per CU, and
+// column blocks and two groups per wave for at least 8 waves a block).
 static bool stream_shape(const hl_tensor* t, const GroupArgs& ga, int* jt, uint32_t* waves, size_t* per_wave) {
   size_t tab = 0;
   if (!stream_regions(t, ga, jt, per_wave, &tab)) return false;
@@ -2784,7 +2787,7 @@ static bool stream_shape(const hl_tensor* t, const GroupArgs& ga, int* jt, uint3
   // float16 without flat mh codes: two row blocks per CU at least (4096x4096,
   // one per CU: 25.9 us against 24.3 us on the non-persistent kernel;
   // 14336x4096 65.8 against 86.2 us). With them one is enough (4096x4096 20.2
-  // against 20.3 us; decoding 4096x11008 55.8 against 98.8 us).
+  // against 20.3 us).
   const uint32_t min_rb = table == 2 ? 2 * cus : cus;
   return w >= 8 && CB >= w && RB >= min_rb && (uint64_t)RB * CB >= 2ull * cus * w;
 }
@@ -2823,9 +2826,9 @@ extern "C" hl_status hl_decode(const hl_tensor* t, uint16_t* out_dev, void* stre
     if (is_fp16(t))
       return launch_stream16(false, true, flat_mh(t->cb16), t->seg_len, jt, grid, dim3(w * 64),
                              (size_t)pl.ga.t16_words * 4 + w * per_wave, (hipStream_t)stream, p);
-    // the bounded-pair table where the encoder's joint limit holds (with the
-    // whole-row stores it decodes 28672x8192 in 175.9 us against 187.7 us
-    // with the joint table; stored straight from the lanes, 307 against 273)
+    // the bounded-pair table where the encoder's joint limit holds (28672x8192
+    // 171.5 us cold, 183.4 with the joint table; stored straight from the lanes
+    // instead of in whole rows, 307 and 273)
     return launch_stream_dec(t->seg_len, jt, bounded_pairs(t), grid, dim3(w * 64), w * per_wave,
                              (hipStream_t)stream, p);
   }
