@@ -2876,7 +2876,7 @@ static uint64_t used_counter_bytes(uint32_t RB) { return ((uint64_t)RB * 4 + 255
 static double vector_time(const Plan& pl, uint32_t batch, uint32_t cus, uint32_t KS) {
   const uint32_t C = (pl.ga.CB + KS - 1) / KS, w = std::min(pl.waves, C);
   const double unit = 64.0 / pl.ga.S;
-  return ((uint64_t)pl.ga.RB * KS + cus - 1) / cus * (unit * (1 + batch / 16.0) + (C + w - 1) / w) +
+  return (pl.ga.RB * KS + cus - 1) / cus * (unit * (1 + batch / 16.0) + (C + w - 1) / w) +
          (KS > 1 ? 0.5 * unit : 0.0);
 }
 
@@ -2910,6 +2910,7 @@ static void split_shape(const hl_tensor* t, const Plan& pl, uint32_t batch, uint
   if (pl.vector && RB <= kSplitRowBlocks) {
     double best = vector_time(pl, batch, cus, KS);
     for (uint32_t k = KS + 1; k <= ks_cap(CB); ++k) {
+      if ((CB + k - 1) / k == (CB + k - 2) / (k - 1)) continue;  // more parts, none shorter
       const double time = vector_time(pl, batch, cus, k);
       if (time >= 0.95 * best) continue;
       if (xtile_region(t, batch) + split_bytes(pl, batch, k) + used_counter_bytes(RB) > HL_NOALLOC_SCRATCH_BYTES) break;
@@ -3057,6 +3058,7 @@ static hl_status gemv_plan(const hl_tensor* t, hl_dtype x_dtype, uint32_t batch,
 // kCounterBytes) arrival counters; all 0 for bad arguments.
 struct GemvNeed {
   uint64_t tile = 0, parts = 0, counters = 0;
+  bool grows = false;  // the parts are the same for every batch: no smaller one needs more
   uint64_t bytes() const { return tile + parts ? kCounterBytes + tile + parts : 0; }
 };
 static GemvNeed gemv_need(const hl_tensor* t, hl_dtype x_dtype, uint32_t batch) {
@@ -3075,6 +3077,7 @@ static GemvNeed gemv_need(const hl_tensor* t, hl_dtype x_dtype, uint32_t batch) 
     if (x_dtype == HL_F16 || gemv_plan(t, x_dtype, batch, &pl, &mfma, &persistent, &xw) != HL_OK) return need;
   }
   need.tile = xtile_region(t, batch);
+  need.grows = !pl.vector || pl.ga.RB > kSplitRowBlocks;
   if (persistent) return need;
   uint32_t C = 0, KS = 0;
   split_shape(t, pl, batch, &C, &KS);
@@ -3087,10 +3090,16 @@ extern "C" size_t hl_gemv_workspace_bytes(const hl_tensor* t, uint32_t batch) {
   if (!t || t->seg_len == 0 || t->grp_rows == 0 || t->grp_rows > HL_GROUP_SEGS || batch < 1 ||
       batch > HL_MAX_BATCH)
     return 0;
-  // enough for smaller batches too, which may take more parts
+  // enough for smaller batches too, of which the vector kernel may take more parts
   uint64_t bytes = 0;
-  for (uint32_t b = 1; b <= batch; ++b)
-    for (hl_dtype x : {HL_F32, HL_BF16, HL_F16}) bytes = std::max(bytes, gemv_need(t, x, b).bytes());
+  for (hl_dtype x : {HL_F32, HL_BF16, HL_F16}) {
+    if (is_fp16(t) != (x == HL_F16)) continue;
+    for (uint32_t b = batch; b >= 1; --b) {
+      const GemvNeed need = gemv_need(t, x, b);
+      bytes = std::max(bytes, need.bytes());
+      if (need.grows) break;
+    }
+  }
   return (size_t)bytes;
 }
 
