@@ -1107,7 +1107,15 @@ __device__ inline void mfma_finish(const GemvArgs& p, const f32x4_t& acc, float*
 // per group, unrolled so that every wait on a prefetch is exact.
 template <int SP, bool XT, bool ONE>
 __global__ void __launch_bounds__(1024) gemv_mfma_kernel(GemvArgs p) {
-  constexpr int KP = SP < 8 ? SP : SP == 8 ? 8 : 4;  // 16 steps at depth 8 exceed 128 VGPRs
+  // 16 steps at depth 8 exceed 128 VGPRs; with the bounded-pair table they
+  // take all 128 at any depth, so one value is kept in the last of them through
+  // the loop, which no shift count can then be in (see shift_window), and at
+  // depth 2 the others do without it (14336x4096 35.1 us, 36.2 at depth 4, with
+  // the joint table 49.8)
+  constexpr bool kPin = ONE && SP == 16;
+  constexpr int KP = SP < 8 ? SP : SP == 8 ? 8 : kPin ? 2 : 4;
+  uint32_t pin = 0;
+  if constexpr (kPin) asm volatile("v_mov_b32 %0, 0" : "={v127}"(pin));
   const GroupArgs& a = p.g;
   const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t waves = blockDim.x >> 6;
@@ -1188,6 +1196,7 @@ __global__ void __launch_bounds__(1024) gemv_mfma_kernel(GemvArgs p) {
 #pragma unroll
       for (int k = 0; k < KP; ++k) {
         uint32_t e[8];
+        if constexpr (kPin) asm volatile("" : "+{v127}"(pin));
         small_decode8<ONE>(sc, sc_off, jmax, pd, e);
         uint4 wv;
         wv.x = pack_pair(rw[k].x, 0, e[0], e[1]);
@@ -2416,10 +2425,7 @@ static hl_status make_plan(const hl_tensor* t, uint32_t extra_words_per_wave, bo
     a.t16_words = lay.words;
   }
   pl->vector = raw_lds;
-  // (segments of 128 weights, 16 steps, keep the joint table: the code of their
-  // form with the single table has a shift count in the last of its 128
-  // registers, see shift_window; its products were wrong in 1 call of 15)
-  pl->one = !raw_lds && t->seg_len <= 64 && longest_exponent_code(t) <= (uint32_t)kBpBits;
+  pl->one = !raw_lds && longest_exponent_code(t) <= (uint32_t)kBpBits;
   const size_t tab_static = is_fp16(t) ? 0 : (size_t)(pl->one ? kBpN : kLutN + kAuxWords) * 4;
   pl->tab_static = tab_static;
   const size_t tab_dyn = is_fp16(t) ? (size_t)a.t16_words * 4 : 0;
@@ -2624,9 +2630,7 @@ static hl_status launch_mfma_x(uint32_t steps, dim3 grid, dim3 block, size_t lds
     case 2: return launch(gemv_mfma_kernel<2, XT, ONE>, grid, block, lds, s, p);
     case 4: return launch(gemv_mfma_kernel<4, XT, ONE>, grid, block, lds, s, p);
     case 8: return launch(gemv_mfma_kernel<8, XT, ONE>, grid, block, lds, s, p);
-    case 16:
-      if constexpr (ONE) return HL_EUNSUPPORTED;  // never planned
-      else return launch(gemv_mfma_kernel<16, XT, false>, grid, block, lds, s, p);
+    case 16: return launch(gemv_mfma_kernel<16, XT, ONE>, grid, block, lds, s, p);
     default: return HL_EUNSUPPORTED;
   }
 }
